@@ -92,11 +92,10 @@ typedef struct gs_opts {
   float t_min;            /* 1e-4 */
   float bg[3];            /* background colour, 0 */
   int32_t waves_per_tile; /* 0 or tile_w * tile_h / 64 (fixed by the tile shape) */
-  int32_t block_w;        /* each wave's 8x8 sub-tile is walked as blocks of block_w x block_w pixels, each in
-                             lock-step over the staged records whose pixel rectangle meets it: 2, 4 or 8 (0 = 4).
-                             Results are identical (a record is skipped only where its rectangle misses the
-                             pixel) */
-  int32_t batch_depth;    /* records staged per thread per round: 1 or 2 (0 = 1); results identical */
+  int32_t block_w;        /* 0, 2, 4 or 8: accepted for callers that set it.  Every 8x8 sub-tile is walked as 4x4-pixel
+                             blocks whatever the value (the results never depended on it, and 2x2 and 8x8 blocks
+                             were slower) */
+  int32_t batch_depth;    /* records staged per thread per round of the forward: 1 or 2 (0 = 1); results identical */
   int32_t seg_len;        /* compositing (gs_render_fwd, gs_render_bwd): a tile list longer than this is split
                              into depth segments of this many records, composited by separate workgroups and
                              joined per pixel (transmittance products, then prefix sums); 0 = default 512,
@@ -184,10 +183,11 @@ typedef struct gs_frame {
   int32_t* seg_first;   /* [n_tiles]: exclusive scan of seg_count = first work item of that tile */
   int32_t* items;       /* [item_cap][4]: work items of the compositing calls, split tiles first:
                            {tile, segment, first slot of the tile or -1, schedule position} */
-  float* seg;           /* [seg_cap][6][tile_w * tile_h]: per-segment pixel state of split tiles */
+  float* seg;           /* [seg_cap, in frames of 2048 tiles or more item_cap][6][tile_w * tile_h]: per-segment pixel
+                           state of split tiles; in the backward of such frames also the upstream gradient of whole
+                           tiles; and behind it [n_tiles] each tile's loss */
   float* split;         /* [long_cap][12][tile_w * tile_h]: per-pixel stop state and upstream gradient */
-  float* loss;          /* [64]: loss[0] the loss value written by gs_render_bwd in loss mode; loss[1..32] its
-                           partial sums */
+  float* loss;          /* [64]: loss[0] the loss value written by gs_render_bwd in loss mode */
   int32_t* scratch;     /* sort histograms and scan partials */
   size_t scratch_ints;
 } gs_frame;

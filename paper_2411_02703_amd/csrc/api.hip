@@ -130,7 +130,9 @@ Layout make_layout(int64_t n, int V, int n_tiles, int64_t cap, const gs_opts* op
   L.segcount = take((size_t)n_tiles * 4);
   L.segfirst = take((size_t)n_tiles * 4);
   L.items = take((size_t)L.item_cap * 16);
-  L.seg = take((size_t)L.seg_cap * 6 * NT * 4);
+  // the segments' slots, in large frames one per work item (the whole tiles of the backward keep their pixels'
+  // upstream gradients in theirs), and behind them a float per tile, its loss
+  L.seg = take((size_t)gsk::seg_slots(n_tiles, L.seg_cap) * 6 * NT * 4 + (size_t)n_tiles * 4);
   L.split = take((size_t)L.long_cap * 12 * NT * 4);
   int64_t big = n > n_tiles ? n : n_tiles;
   if (L.rec_cap > big) big = L.rec_cap;
@@ -384,12 +386,11 @@ int gs_composite_bwd(const gs_frame* f, const gs_opts* o, const gs_images* fwd, 
   if (o->tile_w != f->tile_w || o->tile_h != f->tile_h) return fail(GS_ERR_ARG, "tile size differs from the frame");
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (l->tgt_rgb) {
-    // counts the valid target depths per view and clears the loss slots
-    GS_HIP(gs_launch::count_valid(*f, l->tgt_depth, f->max_view_pixels, f->loss, 1 + gsk::kLossSlots, st),
-           "gs_composite_bwd: valid depth");
+    // the valid target depths per view
+    GS_HIP(gs_launch::count_valid(*f, l->tgt_depth, f->max_view_pixels, st), "gs_composite_bwd: valid depth");
   }
   GS_HIP(gs_launch::render_bwd(*f, *o, fwd, *l, st), "gs_composite_bwd");
-  if (l->tgt_rgb) GS_HIP(gs_launch::loss_total(f->loss, st), "gs_composite_bwd: loss total");
+  if (l->tgt_rgb) GS_HIP(gs_launch::loss_total(*f, st), "gs_composite_bwd: loss total");
   return GS_OK;
 }
 

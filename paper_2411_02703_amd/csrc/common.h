@@ -9,8 +9,17 @@
 namespace gsk {
 
 constexpr int kWave = 64;
-// Partial sums of the loss (frame->loss[1 .. kLossSlots]); the frame holds 64 floats for the loss.
+// Partial sums of the SSIM term (its loss_out[1 .. kLossSlots]).
 constexpr int kLossSlots = 32;
+
+// Frames of at least this many tiles run the forward of the backward's whole tiles in the kernel of the segments'
+// sums (where it issues 1.7 times as fast) and keep its result in a state slot per work item; smaller frames, which
+// leave the chip partly idle and wait for their longest tile, run it in the backward's kernel (48 tiles of 54 records:
+// 20 us in one kernel, 11 + 21 us in two).
+constexpr int kWholeTiles = 2048;
+
+// Slots of a frame's segment state.
+inline int seg_slots(int n_tiles, int seg_cap) { return n_tiles >= kWholeTiles ? n_tiles + seg_cap : seg_cap; }
 
 // Options as the kernels see them (passed by value).
 struct DevOpts {
@@ -42,6 +51,11 @@ __device__ __forceinline__ int lane_id() { return __lane_id(); }
 __device__ __forceinline__ uint64_t lanemask_lt() {
   const int l = __lane_id();
   return l == 0 ? 0ull : (~0ull >> (64 - l));
+}
+
+// n plus the number of set bits of m below this lane.
+__device__ __forceinline__ int rank_in(uint64_t m, int n) {
+  return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, (uint32_t)n));
 }
 
 // DPP move of a float with control CTRL; lanes without a valid source (bound_ctrl) or in a masked row read 0.
@@ -117,8 +131,13 @@ __device__ __forceinline__ int xcd_remap(int b, int nblocks) {
   return (b & 7) * per + (b >> 3);
 }
 
-// View of a global tile: largest v with tile_offset <= tile (uniform scalar loop, n_views <= 64).
+// View of a global tile: largest v with tile_offset <= tile (n_views <= 64; every lane of the wave asks for the same
+// tile).  Past a few views the lanes read an offset each: a scalar loop waits for one load after the other.
 __device__ __forceinline__ int view_of_tile(const gs_camera* __restrict__ cams, int n_views, int tile) {
+  if (n_views > 4) {
+    const int l = lane_id();
+    return __popcll(ballot(l < n_views && cams[l < n_views ? l : 0].tile_offset <= tile)) - 1;
+  }
   int v = 0;
   for (int i = 1; i < n_views; ++i)
     if (cams[i].tile_offset <= tile) v = i;
@@ -170,10 +189,9 @@ hipError_t tile_schedule(const gs_frame& f, hipStream_t s);
 hipError_t work_items(const gs_frame& f, hipStream_t s);
 hipError_t render_fwd(const gs_frame& f, const gs_opts& o, const gs_images& out, hipStream_t s);
 hipError_t count_pairs(const gs_frame& f, const gs_opts& o, unsigned long long* counts, hipStream_t s);
-hipError_t count_valid(const gs_frame& f, const float* tgt_depth, int64_t max_pixels, float* loss, int n_loss,
-                       hipStream_t s);
-// loss[0] = sum of the partial sums loss[1 .. kLossSlots]
-hipError_t loss_total(float* loss, hipStream_t s);
+hipError_t count_valid(const gs_frame& f, const float* tgt_depth, int64_t max_pixels, hipStream_t s);
+// frame loss[0] = sum of the tiles' losses that render_bwd left
+hipError_t loss_total(const gs_frame& f, hipStream_t s);
 hipError_t render_bwd(const gs_frame& f, const gs_opts& o, const gs_images* fwd, const gs_loss& l,
                       hipStream_t s);
 hipError_t adam(const gs_params& p, const gs_params& g, const gs_params& m, const gs_params& v,

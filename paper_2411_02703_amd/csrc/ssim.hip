@@ -171,6 +171,13 @@ __global__ __launch_bounds__(kThreads) void k_ssim(const SsimArgs a) {
   }
 }
 
+// loss[0] = sum of the partial sums loss[1 .. kLossSlots]
+__global__ void k_ssim_total(float* __restrict__ loss) {
+  const int l = threadIdx.x;
+  const float sum = gsk::wave_sum_last(l < gsk::kLossSlots ? loss[1 + l] : 0.f);
+  if (l == 63) loss[0] = sum;
+}
+
 }  // namespace
 
 namespace gs_launch {
@@ -202,7 +209,8 @@ hipError_t ssim(const gs_camera* cams_host, const gs_camera* cams_dev, int n_vie
   if (e != hipSuccess) return e;
   k_ssim<<<dim3((unsigned)tiles, 3), kThreads, 0, st>>>(a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  return loss_total(loss, st);
+  k_ssim_total<<<1, 64, 0, st>>>(loss);
+  return hipGetLastError();
 }
 
 }  // namespace gs_launch
