@@ -964,9 +964,9 @@ __global__ __launch_bounds__(TW * TH, 4) void k_render_bwd(const float4* __restr
 // Compositing is a product of transmittances, so per pixel:
 //   1. each segment k walks its records from T = 1 without the stop rule: its transmittance product T_k and
 //      local sums (C, D, V)_k (k_bwd_sums, alongside the unsplit tiles);
-//   2. T_start,k = T_0 T_1 ... T_{k-1} (left to right, k_seg_prefix); the pixel's last live segment k* is the
+//   2. T_start,k = T_0 T_1 ... T_{k-1} (left to right); the pixel's last live segment k* is the
 //      last with T_start,k >= t_min, and only there can the stop rule end the walk: that segment is walked
-//      again from T_start,k* with the stop rule (k_seg_stop);
+//      again from T_start,k* with the stop rule (k_seg_stop; not where the forward images are given);
 //   3. the final values are sum_{k<k*} T_start,k (C, D, V)_k plus segment k*'s stopped sums plus the
 //      background; from them the upstream gradient g, S and each segment's start state (T_start,k,
 //      P_start,k = g . sum_{j<k} contribution_j) (k_seg_combine);
@@ -1016,6 +1016,12 @@ __device__ __forceinline__ void for_items(int count, int32_t* ctr, Body body) {
   }
 }
 
+// A whole tile of fewer records than this has its forward in the backward's block instead of k_bwd_sums: the sums that
+// k_bwd_sums leaves behind (20 B written and read per pixel) cost as much as a short list's sweep.  A step over 16.5 k
+// tiles of 13 records: 439 us with every tile's forward in k_bwd_sums, 434 us with this rule at 16, 32 or 64; a
+// keyframe of long lists: 1649, 1651, 1651 and 1653 us.
+constexpr int kOwnForward = 32;
+
 // Step 1 of the backward: segments of the split tiles run segment_sums; whole tiles run the forward sweep up to the
 // upstream gradient and leave it (g and S, six floats a pixel) in the segment state's slot of their work item (with
 // forward images, and in small frames, k_bwd_main forms it itself).  A kernel of its own, since the forward's walk
@@ -1034,9 +1040,9 @@ __global__ __launch_bounds__(TW * TH, 6) void k_bwd_sums(const float4* __restric
     tile_at<G>(cams, V, it.x, t);
     if (it.z >= 0) {
       segment_sums<G>(s, rec, vals, range[it.x], it, t, op, g);
-    } else if (!HAVE_FWD) {
+    } else if (const int2 rg = range[it.x]; !HAVE_FWD && rg.y - rg.x >= kOwnForward) {
       float v[6];
-      tile_upstream<G, false, LOSS>(s, rec, vals, range[it.x], t, op, a, it.w, v[0], v[1], v[2], v[3], v[4], v[5]);
+      tile_upstream<G, false, LOSS>(s, rec, vals, rg, t, op, a, it.w, v[0], v[1], v[2], v[3], v[4], v[5]);
       float* o = g.seg + (size_t)b * 6 * G::NT + threadIdx.x;
 #pragma unroll
       for (int i = 0; i < 6; ++i)
@@ -1068,6 +1074,14 @@ __global__ __launch_bounds__(TW * TH, 6) void k_fwd_main(const float4* __restric
   write_pixel(t, op, T, Cr, Cg, Cb, D, Vs, out_rgb, out_depth, out_vis);
 }
 
+// Segments of a split tile whose loads the combine steps keep in flight together (a tile may have a hundred
+// segments, and the running products make each pixel's pass serial).
+constexpr int kSegBatch = 4;
+constexpr int kPrefixBatch = 16;
+
+// Step 2: the last live segment of each pixel walks again, from its start transmittance and with the stop rule.  Every
+// segment forms its own start transmittances (a pass of its own over them took 5 us in frames without a split tile and
+// 23 us in one of 10 k).
 template <int TW, int TH, int DEPTH, bool PERSIST = false>
 __global__ __launch_bounds__(TW * TH, 6) void k_seg_stop(const float4* __restrict__ rec, const int32_t* __restrict__ vals,
                                                       const int2* __restrict__ range,
@@ -1081,10 +1095,27 @@ __global__ __launch_bounds__(TW * TH, 6) void k_seg_stop(const float4* __restric
     tile_at<G>(cams, V, it.x, t);
     const int2 rg = range[it.x];
     const int n = (rg.y - rg.x + g.len - 1) / g.len;
-    // start transmittances of this segment and the next (k_seg_prefix)
-    const float* sp = g.seg + (size_t)(it.z + it.y) * 6 * G::NT + threadIdx.x;
-    const float Ts = sp[0];
-    const bool last = t.inside && Ts >= op.t_min && (it.y == n - 1 || sp[6 * G::NT] < op.t_min);
+    // start transmittances of this segment and the next: the products of the segments before them, left to right
+    // (a dead pixel stays dead, so the wave stops reading once all of its pixels are)
+    const float* sp = g.seg + (size_t)it.z * 6 * G::NT + threadIdx.x;
+    float Ts = 1.f, Te = 1.f;
+    for (int k0 = 0; k0 <= it.y; k0 += kPrefixBatch) {
+      if (!__builtin_amdgcn_ballot_w64(Te >= op.t_min)) {
+        Ts = Te;
+        break;
+      }
+      float v[kPrefixBatch];
+#pragma unroll
+      for (int i = 0; i < kPrefixBatch; ++i) v[i] = sp[(size_t)min(k0 + i, it.y) * 6 * G::NT];
+#pragma unroll
+      for (int i = 0; i < kPrefixBatch; ++i) {
+        if (k0 + i > it.y) break;
+        Ts = Te;
+        Te = Ts * v[i];
+      }
+    }
+    const bool last = t.inside && Ts >= op.t_min && (it.y == n - 1 || Te < op.t_min);
+    if (!__syncthreads_or(last)) return;
     float T = Ts, Cr = 0.f, Cg = 0.f, Cb = 0.f, D = 0.f, Vs = 0.f;
     forward_walk<G, true>(s, rec, vals, segment_range<G>(rg, it.y, g.len), t, op, last, T, Cr, Cg, Cb, D, Vs);
     if (last) {
@@ -1099,80 +1130,52 @@ __global__ __launch_bounds__(TW * TH, 6) void k_seg_stop(const float4* __restric
   });
 }
 
-// Segments of a split tile whose loads the combine steps keep in flight together (a tile may have a hundred
-// segments, and the running products make each pixel's pass serial).
-constexpr int kSegBatch = 4;
-constexpr int kPrefixBatch = 16;
-
-// Step 2, first half: per pixel, the start transmittance T_start,k = T_0 T_1 ... T_{k-1} of every segment of a
-// split tile (the left-to-right product), written over the segment's own product T_k.  Once it is below
-// t_min, so is every later one (each T_k <= 1), and only that comparison is used: those are written as 0.
-template <int TW, int TH>
-__global__ __launch_bounds__(TW * TH) void k_seg_prefix(SegArgs g, DevOpts op) {
-  using G = Geo<TW, TH, 1>;
-  const int l = blockIdx.x;
-  if (l >= g.counters[194]) return;
-  const int n = g.seg_count[l];
-  constexpr size_t SS = 6 * G::NT;
-  float* sp = g.seg + (size_t)g.seg_first[l] * SS + threadIdx.x;
-  float Tr = 1.f;
-  for (int k0 = 0; k0 < n; k0 += kPrefixBatch) {
-    const bool live = Tr >= op.t_min;
-    float v[kPrefixBatch];
-#pragma unroll
-    for (int i = 0; i < kPrefixBatch; ++i) v[i] = live ? sp[(size_t)min(k0 + i, n - 1) * SS] : 0.f;
-#pragma unroll
-    for (int i = 0; i < kPrefixBatch; ++i) {
-      if (k0 + i >= n) break;
-      sp[(size_t)(k0 + i) * SS] = Tr >= op.t_min ? Tr : 0.f;
-      Tr = Tr * v[i];
-    }
-  }
-}
-
-// Step 3, first half: the pixel's last live segment ks (the last whose start transmittance, from
-// k_seg_prefix, is at least t_min) and its final sums (C, D, V) and transmittance.  One pass: while the start
+// Step 3, first half: the pixel's last live segment ks (the last whose start transmittance, the product of the
+// segments before it, is at least t_min) and its final sums (C, D, V) and transmittance.  One pass: while the start
 // transmittance of segment k is at least t_min, k is the candidate and the weighted sum of the segments
-// before it is kept aside; the sums are formed in segment order.
-template <class G>
+// before it is kept aside; the sums are formed in segment order.  SUMS = false: only ks.
+template <class G, bool SUMS>
 __device__ __forceinline__ void split_final(const float* sp, const float* xp, int n, const TileCtx& t,
                                             const DevOpts& op, int& ks, float& Tf, float& Cr, float& Cg, float& Cb,
                                             float& D, float& Vs) {
   constexpr size_t SS = 6 * G::NT;
+  constexpr int BATCH = SUMS ? kSegBatch : kPrefixBatch, W = SUMS ? 6 : 1;
   ks = 0;
   bool more = true;
-  float Rr = 0.f, Rg = 0.f, Rb = 0.f, RD = 0.f, RV = 0.f;  // weighted sums of the segments before k
+  float Ts = 1.f, Rr = 0.f, Rg = 0.f, Rb = 0.f, RD = 0.f, RV = 0.f;  // weighted sums of the segments before k
   Cr = Cg = Cb = D = Vs = 0.f;
-  for (int k0 = 0; k0 < n && more; k0 += kSegBatch) {
-    float v[kSegBatch][6];
+  for (int k0 = 0; k0 < n && more; k0 += BATCH) {
+    float v[BATCH][W];
 #pragma unroll
-    for (int i = 0; i < kSegBatch; ++i) {
+    for (int i = 0; i < BATCH; ++i) {
       const float* q = sp + (size_t)min(k0 + i, n - 1) * SS;
 #pragma unroll
-      for (int c = 0; c < 6; ++c) v[i][c] = q[c * G::NT];
+      for (int c = 0; c < W; ++c) v[i][c] = q[c * G::NT];
     }
 #pragma unroll
-    for (int i = 0; i < kSegBatch; ++i) {
-      const float Ts = v[i][0];
+    for (int i = 0; i < BATCH; ++i) {
       if (k0 + i < n && Ts >= op.t_min) {
         ks = k0 + i;
-        Cr = Rr;
-        Cg = Rg;
-        Cb = Rb;
-        D = RD;
-        Vs = RV;
-        Rr = __builtin_fmaf(Ts, v[i][1], Rr);
-        Rg = __builtin_fmaf(Ts, v[i][2], Rg);
-        Rb = __builtin_fmaf(Ts, v[i][3], Rb);
-        RD = __builtin_fmaf(Ts, v[i][4], RD);
-        RV = __builtin_fmaf(Ts, v[i][5], RV);
+        if constexpr (SUMS) {
+          Cr = Rr;
+          Cg = Rg;
+          Cb = Rb;
+          D = RD;
+          Vs = RV;
+          Rr = __builtin_fmaf(Ts, v[i][1], Rr);
+          Rg = __builtin_fmaf(Ts, v[i][2], Rg);
+          Rb = __builtin_fmaf(Ts, v[i][3], Rb);
+          RD = __builtin_fmaf(Ts, v[i][4], RD);
+          RV = __builtin_fmaf(Ts, v[i][5], RV);
+        }
+        Ts *= v[i][0];
       } else {
         more = false;
       }
     }
   }
   Tf = 1.f;
-  if (t.inside) {
+  if (SUMS && t.inside) {
     Tf = xp[0];
     Cr += xp[1 * G::NT];
     Cg += xp[2 * G::NT];
@@ -1196,12 +1199,12 @@ __global__ __launch_bounds__(TW * TH) void k_seg_fwd_out(const gs_camera* __rest
   const float* xp = g.split + (size_t)l * 12 * G::NT + threadIdx.x;
   int ks;
   float T, Cr, Cg, Cb, D, Vs;
-  split_final<G>(sp, xp, g.seg_count[l], t, op, ks, T, Cr, Cg, Cb, D, Vs);
+  split_final<G, true>(sp, xp, g.seg_count[l], t, op, ks, T, Cr, Cg, Cb, D, Vs);
   write_pixel(t, op, T, Cr, Cg, Cb, D, Vs, out_rgb, out_depth, out_vis);
 }
 
-// Backward of split tiles, step 3: final values (or the forward images), upstream gradient, S and the start
-// state (T_start, P_start) of every segment; T_start = 0 marks a segment after the pixel's end.
+// Backward of split tiles, step 3: final values (or the forward images, which spare step 2), upstream gradient, S and
+// the start state (T_start, P_start) of every segment; T_start = 0 marks a segment after the pixel's end.
 template <int TW, int TH, bool HAVE_FWD, bool LOSS>
 __global__ __launch_bounds__(TW * TH) void k_seg_combine(const gs_camera* __restrict__ cams, int V, DevOpts op,
                                                          BwdArgs a, SegArgs g) {
@@ -1217,7 +1220,7 @@ __global__ __launch_bounds__(TW * TH) void k_seg_combine(const gs_camera* __rest
   int ks;
   float Tf, Cr, Cg, Cb, D, Vs;
   const Upstream u = load_upstream<LOSS>(t, a);
-  split_final<G>(sp, xp, n, t, op, ks, Tf, Cr, Cg, Cb, D, Vs);
+  split_final<G, !HAVE_FWD>(sp, xp, n, t, op, ks, Tf, Cr, Cg, Cb, D, Vs);
   float Cf = __builtin_fmaf(Tf, op.bg[0], Cr), Gf = __builtin_fmaf(Tf, op.bg[1], Cg);
   float Bf = __builtin_fmaf(Tf, op.bg[2], Cb), Df = D, Vf = Vs;
   if (HAVE_FWD && t.inside) {
@@ -1233,7 +1236,7 @@ __global__ __launch_bounds__(TW * TH) void k_seg_combine(const gs_camera* __rest
   pixel_upstream<LOSS>(t, a, u, Cf, Gf, Bf, Df, gr, gg, gb, gd, gv, loss_acc);
   const float S = gr * Cf + gg * Gf + gb * Bf + gd * Df + gv * Vf;
   if (LOSS) store_loss<G>(t, a, l, loss_acc);
-  float Pr = 0.f;
+  float Pr = 0.f, Tr = 1.f;
   for (int k0 = 0; k0 < n; k0 += kSegBatch) {
     // segments up to ks are read (batched); later ones only get T_start = 0
     float v[kSegBatch][6];
@@ -1248,12 +1251,13 @@ __global__ __launch_bounds__(TW * TH) void k_seg_combine(const gs_camera* __rest
       const int k = k0 + i;
       if (k >= n) break;
       float* q = sp + (size_t)k * SS;
-      const float Ts = v[i][0];
+      const float Ts = Tr;
       const float dot =
           k < ks ? Ts * (gr * v[i][1] + gg * v[i][2] + gb * v[i][3] + gd * v[i][4] + gv * v[i][5]) : 0.f;
       q[0] = k <= ks ? Ts : 0.f;
       q[1 * G::NT] = Pr;
       Pr += dot;
+      Tr *= v[i][0];
     }
   }
   xp[6 * G::NT] = gr;
@@ -1279,12 +1283,11 @@ __global__ __launch_bounds__(TW * TH, 4) void k_bwd_main(const float4* __restric
   for_items<PERSIST>(g.counters[192], ctr, [&](int b) {
     const int4 it = g.items[b];
     int2 rg = range[it.x];
-    if (!HAVE_FWD && g.whole && rg.x >= rg.y) return;  // an empty tile: its loss is in
     TileCtx t;
     tile_at<G>(cams, V, it.x, t);
     bool live = t.inside;
     float T = 1.f, P = 0.f, gr, gg, gb, gd, gv, S;
-    if (it.z < 0 && !HAVE_FWD && g.whole) {
+    if (it.z < 0 && !HAVE_FWD && g.whole && rg.y - rg.x >= kOwnForward) {
       const float* v = g.seg + (size_t)b * 6 * G::NT + threadIdx.x;
       gr = v[0 * G::NT];
       gg = v[1 * G::NT];
@@ -1439,8 +1442,6 @@ hipError_t launch_fwd(const gs_frame& f, const DevOpts& op, const gs_images& out
                                                           out.depth, out.vis);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_seg_prefix<TW, TH><<<f.long_cap, bs, 0, st>>>(g, op);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
     k_seg_stop<TW, TH, DEPTH><<<f.seg_cap, bs, 0, st>>>(rec, f.vals[sorted], rng, f.cams, f.n_views, op, g,
                                                             nullptr);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1473,9 +1474,9 @@ hipError_t launch_split_bwd(const gs_frame& f, const DevOpts& op, const BwdArgs&
         rec, vals, rng, f.cams, f.n_views, op, a, g, nullptr);
   }
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_seg_prefix<TW, TH><<<f.long_cap, bs, 0, st>>>(g, op);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (persist) {
+  if (HAVE_FWD) {
+    // the final values are given: only the segments' start states are left to form
+  } else if (persist) {
     auto* ks = k_seg_stop<TW, TH, DEPTH, true>;
     ks<<<resident_grid(ks, bs, f.seg_cap), bs, 0, st>>>(rec, vals, rng, f.cams, f.n_views, op, g, ctr + 1);
   } else {

@@ -43,3 +43,17 @@ def test_lists_around_the_round_sizes_match_the_oracle(gpu_lib, n, tile):
                 img = oracle.forward(32, sc.params(), 1, sc.cams)
                 out["cams"] = sc.cams
                 check_images(out, img, img["near"], f"n={n} {tile}")
+
+
+@pytest.mark.parametrize("size", [(184, 712, 1), (256, 512, 1), (128, 128, 8)])  # 2047, 2048 and 8 x 256 tiles of 8x8
+@pytest.mark.parametrize("n", [31, 32, 33, 70])
+def test_forward_kernel_of_whole_tiles_by_frame_and_list_size(gpu_lib, n, size):
+    w, h, views = size
+    sc = scenes.random_scene(7100 + n, n, w, h, sh_degree=1, views=views, log_scale_mu=0.3, zrange=(3.0, 6.0))
+    sc.opacity[:] = -2.0
+    L, ref, exc, _, scale = grad_reference(sc.params(), 1, sc.cams, tgt_rgb=sc.tgt_rgb, tgt_depth=sc.tgt_depth)
+    for seg in (-1, 64):
+        print("frame", n, size, seg, flush=True)
+        out = run_gpu(sc, tile=(8, 8), targets=True, fused=True, seg=seg)
+        np.testing.assert_allclose(out["loss"], L, rtol=1e-5)
+        check_grads(out["grads"], ref, exc, f"n={n} {size} seg={seg}", scale=scale)
