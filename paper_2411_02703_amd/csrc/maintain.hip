@@ -5,9 +5,8 @@
 // front of the output arrays in their original order.
 //
 // Work: one flag per Gaussian, an exclusive scan of the flags (the library's scan), then a gather of every kept
-// row of the fifteen arrays (five parameter groups x params, m, v) with one thread per element, so reads are
-// coalesced and writes are coalesced runs.  HBM-bound: 3 (44 + 12K) bytes read and at most as many written per
-// Gaussian.
+// row of the fifteen arrays (five parameter groups x params, m, v; see copy_rows).  HBM-bound: 3 (44 + 12K) bytes
+// read and at most as many written per Gaussian.
 #include "common.h"
 
 namespace {
@@ -30,19 +29,80 @@ struct Rows {
   int len[15];  // floats per Gaussian
 };
 
-// blockIdx.y selects the array; element e of it belongs to Gaussian e / len.
-__global__ __launch_bounds__(256) void k_prune_gather(const Rows r, int64_t n, const int32_t* __restrict__ keep,
-                                                      const int32_t* __restrict__ off) {
-  const int a = blockIdx.y;
-  const int len = r.len[a];
-  const float* __restrict__ in = r.in[a];
-  float* __restrict__ out = r.out[a];
-  const int64_t total = n * len;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-    const int64_t i = e / len;
-    if (keep[i]) out[(int64_t)off[i] * len + (e - i * len)] = in[e];
+Rows rows_of(const gs_params& p, const gs_params& m, const gs_params& v, const gs_params& op, const gs_params& om,
+             const gs_params& ov) {
+  const int K3 = 3 * (p.sh_degree + 1) * (p.sh_degree + 1);
+  Rows r;
+  const gs_params* src[3] = {&p, &m, &v};
+  const gs_params* dst[3] = {&op, &om, &ov};
+  for (int k = 0; k < 3; ++k) {
+    r.in[5 * k + 0] = src[k]->means;      r.out[5 * k + 0] = dst[k]->means;      r.len[5 * k + 0] = 3;
+    r.in[5 * k + 1] = src[k]->log_scales; r.out[5 * k + 1] = dst[k]->log_scales; r.len[5 * k + 1] = 3;
+    r.in[5 * k + 2] = src[k]->quats;      r.out[5 * k + 2] = dst[k]->quats;      r.len[5 * k + 2] = 4;
+    r.in[5 * k + 3] = src[k]->opacity;    r.out[5 * k + 3] = dst[k]->opacity;    r.len[5 * k + 3] = 1;
+    r.in[5 * k + 4] = src[k]->sh;         r.out[5 * k + 4] = dst[k]->sh;         r.len[5 * k + 4] = K3;
   }
+  return r;
+}
+
+// A block copies the rows src[0, m) (in LDS) of five arrays to the consecutive rows from row0 on, and blockIdx.y selects
+// parameters or moments.  What bounds it is HBM: reads and writes run element by element over the block's output, which
+// is contiguous, up to four loads a thread in flight, in 16-byte words where both arrays' rows are made of them.  The row
+// of a word is e / units by a multiplication (a 64-bit division per element had made the copy of 1M Gaussians of degree
+// 3 VALU-bound: 514 us pruned, 576 us permuted).
+constexpr int kRowBlock = 256;
+
+template <int B, class T>
+__device__ __forceinline__ void copy_batch(const T* __restrict__ in, T* __restrict__ out, int e, int units, uint32_t inv,
+                                           const int32_t* src) {
+  T v[B];
+#pragma unroll
+  for (int i = 0; i < B; ++i) {
+    const int r = (int)((uint32_t)(e + i * kRowBlock) * inv >> 22);
+    v[i] = in[(int64_t)src[r] * units + (e + i * kRowBlock - r * units)];
+  }
+#pragma unroll
+  for (int i = 0; i < B; ++i) out[e + i * kRowBlock] = v[i];
+}
+
+template <class T>
+__device__ __forceinline__ void copy_units(const T* __restrict__ in, T* __restrict__ out, int64_t row0, int m, int units,
+                                           const int32_t* src) {
+  // e / units = (e inv) >> 22 for e < 256 units, units <= 75: e (inv units - 2^22) < 2^22 and e inv < 2^31
+  const uint32_t inv = ((1u << 22) + (uint32_t)units - 1) / (uint32_t)units;
+  const int total = m * units;
+  out += row0 * units;
+  int e = threadIdx.x;
+  for (; e + 3 * kRowBlock < total; e += 4 * kRowBlock) copy_batch<4>(in, out, e, units, inv, src);
+  if (e + 2 * kRowBlock < total) {
+    copy_batch<3>(in, out, e, units, inv, src);
+    e += 3 * kRowBlock;
+  }
+  for (; e < total; e += kRowBlock) copy_batch<1>(in, out, e, units, inv, src);
+}
+
+__device__ __forceinline__ void copy_rows(const Rows& r, int64_t row0, int m, const int32_t* src) {
+#pragma unroll
+  for (int k = 4; k >= 0; --k) {
+    const int a = 5 * blockIdx.y + k, len = r.len[a];
+    const float* in = r.in[a];
+    float* out = r.out[a];
+    if (len % 4 == 0 && ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0)
+      copy_units(reinterpret_cast<const float4*>(in), reinterpret_cast<float4*>(out), row0, m, len / 4, src);
+    else
+      copy_units(in, out, row0, m, len, src);
+  }
+}
+
+// Block b lists the kept ones of its 256 Gaussians; their output rows are consecutive.
+__global__ __launch_bounds__(kRowBlock) void k_prune_gather(const Rows r, int64_t n, const int32_t* __restrict__ keep,
+                                                            const int32_t* __restrict__ off) {
+  __shared__ int32_t src[kRowBlock];
+  const int64_t g0 = (int64_t)blockIdx.x * kRowBlock, g = g0 + threadIdx.x, last = min(g0 + kRowBlock, n) - 1;
+  const int32_t row0 = off[g0];
+  if (g < n && keep[g]) src[off[g] - row0] = (int32_t)g;
+  __syncthreads();
+  copy_rows(r, row0, off[last] + keep[last] - row0, src);
 }
 
 }  // namespace
@@ -65,20 +125,7 @@ hipError_t prune(const gs_params& p, const gs_params& m, const gs_params& v, flo
   if ((e = scan_exclusive(keep, off, n, scan_scr, st)) != hipSuccess) return e;
   k_prune_total<<<1, 64, 0, st>>>(keep, off, n, n_kept);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  const int K3 = 3 * (p.sh_degree + 1) * (p.sh_degree + 1);
-  Rows r;
-  const gs_params* src[3] = {&p, &m, &v};
-  const gs_params* dst[3] = {&op, &om, &ov};
-  for (int k = 0; k < 3; ++k) {
-    r.in[5 * k + 0] = src[k]->means;      r.out[5 * k + 0] = dst[k]->means;      r.len[5 * k + 0] = 3;
-    r.in[5 * k + 1] = src[k]->log_scales; r.out[5 * k + 1] = dst[k]->log_scales; r.len[5 * k + 1] = 3;
-    r.in[5 * k + 2] = src[k]->quats;      r.out[5 * k + 2] = dst[k]->quats;      r.len[5 * k + 2] = 4;
-    r.in[5 * k + 3] = src[k]->opacity;    r.out[5 * k + 3] = dst[k]->opacity;    r.len[5 * k + 3] = 1;
-    r.in[5 * k + 4] = src[k]->sh;         r.out[5 * k + 4] = dst[k]->sh;         r.len[5 * k + 4] = K3;
-  }
-  int64_t gx = (n * K3 + 255) / 256;
-  if (gx > 16384) gx = 16384;
-  k_prune_gather<<<dim3((unsigned)gx, 15), 256, 0, st>>>(r, n, keep, off);
+  k_prune_gather<<<dim3(blocks, 3), kRowBlock, 0, st>>>(rows_of(p, m, v, op, om, ov), n, keep, off);
   return hipGetLastError();
 }
 
@@ -101,23 +148,36 @@ __device__ __forceinline__ float from_ordered(uint32_t o) {
   return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
 }
 
-__global__ __launch_bounds__(256) void k_bbox(const float* __restrict__ means, int64_t n, uint32_t* __restrict__ box) {
-  uint32_t lo[3] = {~0u, ~0u, ~0u}, hi[3] = {0u, 0u, 0u};
-  for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n; g += (int64_t)gridDim.x * blockDim.x)
+// Few blocks (kBoxBlocks), each reduced in LDS before its six atomics: they all meet in one cache line, about 5 ns each
+// (with six per wave of 2048 blocks the box of 1M means took 560 us).
+constexpr int kBoxBlocks = 128;
+constexpr int kBoxThreads = 1024;
+
+__global__ __launch_bounds__(kBoxThreads) void k_bbox(const float* __restrict__ means, int64_t n,
+                                                      uint32_t* __restrict__ box) {
+  __shared__ uint32_t sh[6][kBoxThreads / 64];
+  uint32_t b[6] = {~0u, ~0u, ~0u, 0u, 0u, 0u};
+#pragma unroll 4
+  for (int64_t g = (int64_t)blockIdx.x * kBoxThreads + threadIdx.x; g < n; g += (int64_t)gridDim.x * kBoxThreads)
     for (int k = 0; k < 3; ++k) {
       const uint32_t o = ordered_bits(means[3 * g + k]);
-      lo[k] = min(lo[k], o);
-      hi[k] = max(hi[k], o);
+      b[k] = min(b[k], o);
+      b[3 + k] = max(b[3 + k], o);
     }
-  for (int k = 0; k < 3; ++k) {
+  for (int k = 0; k < 6; ++k) {
     for (int s = 32; s >= 1; s >>= 1) {
-      lo[k] = min(lo[k], (uint32_t)__shfl_xor((int)lo[k], s));
-      hi[k] = max(hi[k], (uint32_t)__shfl_xor((int)hi[k], s));
+      const uint32_t o = (uint32_t)__shfl_xor((int)b[k], s);
+      b[k] = k < 3 ? min(b[k], o) : max(b[k], o);
     }
-    if ((threadIdx.x & 63) == 0) {
-      atomicMin(box + k, lo[k]);
-      atomicMax(box + 3 + k, hi[k]);
-    }
+    if ((threadIdx.x & 63) == 0) sh[k][threadIdx.x >> 6] = b[k];
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) {
+    const int k = threadIdx.x;
+    uint32_t x = sh[k][0];
+    for (int w = 1; w < kBoxThreads / 64; ++w) x = k < 3 ? min(x, sh[k][w]) : max(x, sh[k][w]);
+    if (k < 3) atomicMin(box + k, x);
+    else atomicMax(box + k, x);
   }
 }
 
@@ -148,18 +208,14 @@ __global__ void k_morton(const float* __restrict__ means, int64_t n, const uint3
   vals[g] = (int32_t)g;
 }
 
-// out row k = in row perm[k], for the fifteen arrays (blockIdx.y), one thread per element.
-__global__ __launch_bounds__(256) void k_permute(const Rows r, int64_t n, const int32_t* __restrict__ perm) {
-  const int a = blockIdx.y;
-  const int len = r.len[a];
-  const float* __restrict__ in = r.in[a];
-  float* __restrict__ out = r.out[a];
-  const int64_t total = n * len;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += stride) {
-    const int64_t k = e / len;
-    out[e] = in[(int64_t)perm[k] * len + (e - k * len)];
-  }
+// out row k = in row perm[k]
+__global__ __launch_bounds__(kRowBlock) void k_permute(const Rows r, int64_t n, const int32_t* __restrict__ perm) {
+  __shared__ int32_t src[kRowBlock];
+  const int64_t k0 = (int64_t)blockIdx.x * kRowBlock;
+  const int m = (int)min((int64_t)kRowBlock, n - k0);
+  if ((int)threadIdx.x < m) src[threadIdx.x] = perm[k0 + threadIdx.x];
+  __syncthreads();
+  copy_rows(r, k0, m, src);
 }
 
 }  // namespace
@@ -186,27 +242,15 @@ hipError_t spatial_order(const gs_params& p, const gs_params& m, const gs_params
   hipError_t e = fill_i32(reinterpret_cast<int32_t*>(box), -1, 3, st);  // lo = all ones
   if (e != hipSuccess) return e;
   if ((e = fill_i32(reinterpret_cast<int32_t*>(box) + 3, 0, 3, st)) != hipSuccess) return e;
-  int64_t nb = (n + 255) / 256;
-  if (nb > 2048) nb = 2048;
-  k_bbox<<<(unsigned)nb, 256, 0, st>>>(p.means, n, box);
+  int64_t nb = (n + kBoxThreads - 1) / kBoxThreads;
+  if (nb > kBoxBlocks) nb = kBoxBlocks;
+  k_bbox<<<(unsigned)nb, kBoxThreads, 0, st>>>(p.means, n, box);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_morton<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(p.means, n, box, k0, v0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = sort_pairs(k0, v0, k1, v1, n, nullptr, n, 64, sort_scr, st)) != hipSuccess) return e;  // back in v0
-  const int K3 = 3 * (p.sh_degree + 1) * (p.sh_degree + 1);
-  Rows r;
-  const gs_params* src[3] = {&p, &m, &v};
-  const gs_params* dst[3] = {&op, &om, &ov};
-  for (int k = 0; k < 3; ++k) {
-    r.in[5 * k + 0] = src[k]->means;      r.out[5 * k + 0] = dst[k]->means;      r.len[5 * k + 0] = 3;
-    r.in[5 * k + 1] = src[k]->log_scales; r.out[5 * k + 1] = dst[k]->log_scales; r.len[5 * k + 1] = 3;
-    r.in[5 * k + 2] = src[k]->quats;      r.out[5 * k + 2] = dst[k]->quats;      r.len[5 * k + 2] = 4;
-    r.in[5 * k + 3] = src[k]->opacity;    r.out[5 * k + 3] = dst[k]->opacity;    r.len[5 * k + 3] = 1;
-    r.in[5 * k + 4] = src[k]->sh;         r.out[5 * k + 4] = dst[k]->sh;         r.len[5 * k + 4] = K3;
-  }
-  int64_t gx = (n * K3 + 255) / 256;
-  if (gx > 16384) gx = 16384;
-  k_permute<<<dim3((unsigned)gx, 15), 256, 0, st>>>(r, n, v0);
+  k_permute<<<dim3((unsigned)((n + kRowBlock - 1) / kRowBlock), 3), kRowBlock, 0, st>>>(
+      rows_of(p, m, v, op, om, ov), n, v0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (perm_out) return hipMemcpyAsync(perm_out, v0, (size_t)n * 4, hipMemcpyDeviceToDevice, st);
   return hipSuccess;
