@@ -448,7 +448,7 @@ int gs_prune(const gs_params* p, const gs_params* m, const gs_params* v, float m
 }
 
 size_t gs_expand_scratch_bytes(int64_t n_old, int64_t M) {
-  return (n_old < 0 || M < 1) ? 0 : 4 * gs_launch::expand_scratch_ints(n_old, M);
+  return (n_old < 0 || M < 1) ? 0 : 4 * gs_launch::expand_scratch_ints(M);
 }
 
 int gs_expand(const gs_params* p, const gs_params* m, const gs_params* v, int64_t n_old, const float* pts,

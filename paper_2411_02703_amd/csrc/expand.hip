@@ -5,14 +5,15 @@
 //      (the map does not yet explain that pixel); points outside the image or behind the near plane are kept.
 //   2. Voxel deduplication and density cap (Sec. III-A): points live in voxels of a fixed size; a point is
 //      accepted while its voxel holds fewer than `cap` points, counting the map's Gaussians and this batch's
-//      earlier points (input order).  Keys are sorted (the library's stable radix sort), so each point's rank in
-//      its voxel and the map's count there come from two binary searches.
+//      earlier points (input order).  The points' keys are sorted (the library's stable radix sort), so each point's
+//      rank in its voxel comes from a binary search; the map's Gaussians find their voxel's run of points by another
+//      and are counted there (only voxels that hold points matter).
 //   3. Initialisation (Sec. III-E): mean = the point, log-scales = log sqrt of the mean squared distance to its 3
 //      nearest accepted neighbours (>= 1e-7), identity rotation, opacity logit = inverse sigmoid of the initial
 //      opacity, SH degree-0 coefficients from the colour, higher bands 0, Adam moments 0.  The neighbours come
 //      from a uniform grid over the accepted points (sorted cell keys, ring search with an exact stopping rule:
-//      after ring k every unvisited point is at least k cell sizes away); a point whose third neighbour is not
-//      settled within kMaxRing rings is searched by brute force, a wave per point.
+//      after ring k every unvisited point is at least k cell sizes away), sixteen lanes a point; a point whose third
+//      neighbour is not settled within kMaxRing rings is searched by brute force, a wave per point.
 // Accepted points are appended after the n_old existing Gaussians in their input order.
 #include "common.h"
 
@@ -74,27 +75,58 @@ __global__ void k_point_keys(const float* __restrict__ pts, int64_t M, ExpandCam
   vals[i] = (int32_t)i;
 }
 
-// voxel keys of the existing Gaussians
-__global__ void k_map_keys(const float* __restrict__ means, int64_t N, float voxel, uint64_t* __restrict__ keys,
-                           int32_t* __restrict__ vals) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= N) return;
-  int cc[3];
-  keys[j] = cell_of(means[3 * j], means[3 * j + 1], means[3 * j + 2], 0.f, voxel, cc) ? pack(cc) : kInvalid;
-  vals[j] = (int32_t)j;
+// The map's Gaussians per point voxel, counted at the voxel's first sorted point.  Latency-bound: a binary search over
+// the points' keys per Gaussian (they fit the L2), kTop levels of it in LDS.  (Sorting the keys of 1M Gaussians instead
+// took 24 launches and 350 us.)  Counts stop at the cap, beyond which they change nothing, and a wave whose lanes share
+// a voxel adds once, so that a crowded voxel does not become a queue of atomics.
+constexpr int kTop = 1024;
+
+__global__ __launch_bounds__(256) void k_map_count(const float* __restrict__ means, int64_t N, float voxel,
+                                                   const uint64_t* __restrict__ pk, int M, int cap,
+                                                   int32_t* __restrict__ have) {
+  __shared__ uint64_t top[kTop];  // top[i] = the last key of the i-th of kTop stretches of `step` keys
+  const int step = (M + kTop - 1) / kTop;
+  for (int i = threadIdx.x; i < kTop; i += 256) {
+    const int64_t e = (int64_t)(i + 1) * step - 1;
+    top[i] = e < M ? pk[e] : kInvalid;
+  }
+  __syncthreads();
+  for (int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x; j < N; j += (int64_t)gridDim.x * 256) {
+    int cc[3], at = -1;
+    if (cell_of(means[3 * j], means[3 * j + 1], means[3 * j + 2], 0.f, voxel, cc)) {
+      const uint64_t k = pack(cc);
+      int b = 0;  // the first stretch whose last key is >= k (valid keys are below kInvalid)
+      for (int h = kTop / 2; h >= 1; h >>= 1) b += top[b + h - 1] < k ? h : 0;
+      int lo = min(b * step, M), hi = min(lo + step, M);
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (pk[mid] < k) lo = mid + 1; else hi = mid;
+      }
+      if (lo < M && pk[lo] == k && have[lo] < cap) at = lo;
+    }
+    const uint64_t need = __ballot(at >= 0);
+    if (need) {
+      const int lead = __builtin_ctzll(need), first = __shfl(at, lead);
+      const uint64_t same = __ballot(at == first);
+      if (at == first) {
+        if ((int)__lane_id() == lead) atomicAdd(have + at, (int)__popcll(same));
+      } else if (at >= 0) {
+        atomicAdd(have + at, 1);
+      }
+    }
+  }
 }
 
 // 2. acceptance: rank of the point in its voxel (sorted, stable) plus the map's count there, against the cap
 __global__ void k_accept(const uint64_t* __restrict__ pk, const int32_t* __restrict__ pv, int64_t M,
-                         const uint64_t* __restrict__ mk, int64_t N, int cap, int32_t* __restrict__ accept) {
+                         const int32_t* __restrict__ have, int cap, int32_t* __restrict__ accept) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= M) return;
   const uint64_t k = pk[s];
   int ok = 0;
   if (k != kInvalid) {
-    const int64_t rank = s - lower_bound(pk, s, k);
-    const int64_t have = N > 0 ? lower_bound(mk, N, k + 1) - lower_bound(mk, N, k) : 0;
-    ok = have + rank < cap;
+    const int64_t first = lower_bound(pk, s, k);
+    ok = have[first] + (s - first) < cap;
   }
   accept[pv[s]] = ok;
 }
@@ -137,50 +169,94 @@ __device__ __forceinline__ float spacing_log_scale(const float b[3]) {
   return 0.5f * logf(d2);
 }
 
-// 3b. ring search over the sorted cells; the log-scale goes to the new Gaussian's row, unsettled points to a list
-__global__ void k_knn(const float* __restrict__ pts, const uint64_t* __restrict__ ck, const int32_t* __restrict__ cv,
-                      const int32_t* __restrict__ count, float cell, const int32_t* __restrict__ off,
-                      float* __restrict__ out_ls, int32_t* __restrict__ brute, int32_t* __restrict__ n_brute) {
-  const int64_t A = count[0];
+// The sorted accepted points' positions, so that a cell's points are read in one run.
+__global__ void k_sorted_points(const float* __restrict__ pts, const int32_t* __restrict__ cv,
+                                const int32_t* __restrict__ count, float4* __restrict__ sp) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= A) return;
+  if (s >= count[0]) return;
   const int i = cv[s];
-  const float x = pts[3 * i], y = pts[3 * i + 1], z = pts[3 * i + 2];
-  int c0[3];
-  if (!cell_of(x, y, z, 0.f, cell, c0)) {
-    brute[atomicAdd(n_brute, 1)] = (int)s;
-    return;
+  sp[s] = make_float4(pts[3 * i], pts[3 * i + 1], pts[3 * i + 2], __int_as_float(i));
+}
+
+// The smallest three of `lanes` (a power of two) neighbouring lanes' sorted triples, in every one of them: three rounds
+// of a minimum, whose lowest holder drops it.
+template <int LANES>
+__device__ __forceinline__ void merge3(float b[3]) {
+  float best[3];
+  const int lane = __lane_id();
+  const uint64_t group = LANES == 64 ? ~0ull : ((1ull << (LANES & 63)) - 1) << (lane & ~(LANES - 1));
+  for (int r = 0; r < 3; ++r) {
+    float m = b[0];
+    for (int sh = LANES / 2; sh >= 1; sh >>= 1) m = fminf(m, __shfl_xor(m, sh));
+    best[r] = m;
+    const uint64_t hold = __ballot(b[0] == m && m < INFINITY) & group;
+    if (hold && lane == __builtin_ctzll(hold)) {
+      b[0] = b[1];
+      b[1] = b[2];
+      b[2] = INFINITY;
+    }
   }
+  for (int k = 0; k < 3; ++k) b[k] = best[k];
+}
+
+// 3b. ring search over the sorted cells; the log-scale goes to the new Gaussian's row, unsettled points to a list.
+// Latency-bound: kKnnLanes lanes share a point, each taking rows of cells along x, which are one run of the sorted keys
+// (x is the key's lowest field): one binary search a row, where a search per cell, all by one thread, took 765 us for
+// 100k points.  Rings 0 and 1 go together (ring 0 settles only a point with three copies, which ring 1 cannot change);
+// in a later ring the rows inside the ring before are left with their two end cells.
+constexpr int kKnnLanes = 16;
+
+__device__ __forceinline__ void search_run(const float4* __restrict__ sp, const uint64_t* __restrict__ ck, int64_t A,
+                                           uint64_t from, uint64_t to, int64_t s, float4 p, float b[3]) {
+  for (int64_t j = lower_bound(ck, A, from); j < A && ck[j] <= to; ++j) {
+    if (j == s) continue;
+    const float4 q = sp[j];
+    const float ex = q.x - p.x, ey = q.y - p.y, ez = q.z - p.z;
+    push3(ex * ex + ey * ey + ez * ez, b);
+  }
+}
+
+__global__ __launch_bounds__(256) void k_knn(const float4* __restrict__ sp, const uint64_t* __restrict__ ck,
+                                             const int32_t* __restrict__ count, float cell,
+                                             const int32_t* __restrict__ off, float* __restrict__ out_ls,
+                                             int32_t* __restrict__ brute, int32_t* __restrict__ n_brute) {
+  const int64_t A = count[0];
+  const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kKnnLanes;
+  const int sub = threadIdx.x % kKnnLanes;
+  if (s >= A) return;  // (the whole group)
+  const float4 p = sp[s];
+  int c0[3];
+  const bool in_range = cell_of(p.x, p.y, p.z, 0.f, cell, c0);
   float b[3] = {INFINITY, INFINITY, INFINITY};
-  for (int ring = 0; ring <= kMaxRing; ++ring) {
-    for (int dz = -ring; dz <= ring; ++dz)
-      for (int dy = -ring; dy <= ring; ++dy)
-        for (int dx = -ring; dx <= ring; ++dx) {
-          if (max(abs(dx), max(abs(dy), abs(dz))) != ring) continue;  // the shell of this ring only
-          const int cc[3] = {c0[0] + dx, c0[1] + dy, c0[2] + dz};
-          if (abs(cc[0]) >= kBias || abs(cc[1]) >= kBias || abs(cc[2]) >= kBias) continue;
-          const uint64_t key = pack(cc);
-          for (int64_t j = lower_bound(ck, A, key); j < A && ck[j] == key; ++j) {
-            if (j == s) continue;
-            const int q = cv[j];
-            const float ex = pts[3 * q] - x, ey = pts[3 * q + 1] - y, ez = pts[3 * q + 2] - z;
-            push3(ex * ex + ey * ey + ez * ez, b);
-          }
-        }
+  for (int ring = 1; in_range && ring <= kMaxRing; ++ring) {
+    const int side = 2 * ring + 1;
+    const int x0 = max(c0[0] - ring, 1 - kBias), x1 = min(c0[0] + ring, kBias - 1);
+    float mine[3] = {INFINITY, INFINITY, INFINITY};
+    for (int row = sub; row < side * side; row += kKnnLanes) {
+      const int dy = row % side - ring, dz = row / side - ring;
+      const int y = c0[1] + dy, z = c0[2] + dz;
+      if (abs(y) >= kBias || abs(z) >= kBias) continue;
+      const int l[3] = {x0, y, z}, h[3] = {x1, y, z};
+      if (ring == 1 || max(abs(dy), abs(dz)) == ring) {
+        search_run(sp, ck, A, pack(l), pack(h), s, p, mine);
+      } else {  // the ends only, where they are in the key range
+        if (c0[0] - ring == x0) search_run(sp, ck, A, pack(l), pack(l), s, p, mine);
+        if (c0[0] + ring == x1) search_run(sp, ck, A, pack(h), pack(h), s, p, mine);
+      }
+    }
+    merge3<kKnnLanes>(mine);
+    for (int k = 0; k < 3; ++k) push3(mine[k], b);
     const float reach = (float)ring * cell;
     if (b[2] <= reach * reach) {
-      const float ls = spacing_log_scale(b);
-      float* o = out_ls + 3 * (int64_t)off[i];
-      o[0] = o[1] = o[2] = ls;
+      if (sub < 3) out_ls[3 * (int64_t)off[__float_as_int(p.w)] + sub] = spacing_log_scale(b);
       return;
     }
   }
-  brute[atomicAdd(n_brute, 1)] = (int)s;
+  if (sub == 0) brute[atomicAdd(n_brute, 1)] = (int)s;
 }
 
 // 3c. brute force for the unsettled points: a wave per point over every accepted point, then a wave reduction
-__global__ __launch_bounds__(256) void k_knn_brute(const float* __restrict__ pts, const int32_t* __restrict__ cv,
-                                                   const int32_t* __restrict__ count,
+__global__ __launch_bounds__(256) void k_knn_brute(const float4* __restrict__ sp, const int32_t* __restrict__ count,
                                                    const int32_t* __restrict__ brute,
                                                    const int32_t* __restrict__ n_brute,
                                                    const int32_t* __restrict__ off, float* __restrict__ out_ls) {
@@ -190,32 +266,18 @@ __global__ __launch_bounds__(256) void k_knn_brute(const float* __restrict__ pts
   const int64_t n_waves = ((int64_t)gridDim.x * blockDim.x) >> 6;
   for (int64_t w = wave; w < n_brute[0]; w += n_waves) {
     const int64_t s = brute[w];
-    const int i = cv[s];
-    const float x = pts[3 * i], y = pts[3 * i + 1], z = pts[3 * i + 2];
+    const float4 p = sp[s];
     float b[3] = {INFINITY, INFINITY, INFINITY};
+#pragma unroll 4
     for (int64_t j = lane; j < A; j += 64) {
-      if (j == s) continue;
-      const int q = cv[j];
-      const float ex = pts[3 * q] - x, ey = pts[3 * q + 1] - y, ez = pts[3 * q + 2] - z;
-      push3(ex * ex + ey * ey + ez * ez, b);
+      const float4 q = sp[j];
+      const float ex = q.x - p.x, ey = q.y - p.y, ez = q.z - p.z;
+      push3(j == s ? INFINITY : ex * ex + ey * ey + ez * ez, b);
     }
-    // merge the lanes' three smallest: three rounds of a wave minimum, removing the winner each time
-    float best[3];
-    for (int r = 0; r < 3; ++r) {
-      float m = b[0];
-      for (int sh = 32; sh >= 1; sh >>= 1) m = fminf(m, __shfl_xor(m, sh));
-      best[r] = m;
-      // the lowest lane holding the minimum drops it
-      const uint64_t hold = __ballot(b[0] == m && m < INFINITY);
-      if (hold && lane == __builtin_ctzll(hold)) {
-        b[0] = b[1];
-        b[1] = b[2];
-        b[2] = INFINITY;
-      }
-    }
+    merge3<64>(b);
     if (lane == 0) {
-      const float ls = spacing_log_scale(best);
-      float* o = out_ls + 3 * (int64_t)off[i];
+      const float ls = spacing_log_scale(b);
+      float* o = out_ls + 3 * (int64_t)off[__float_as_int(p.w)];
       o[0] = o[1] = o[2] = ls;
     }
   }
@@ -227,60 +289,74 @@ struct NewRows {
   float* m[5]; float* v[5];  // means, log_scales, quats, opacity, sh of the moments
 };
 
-__global__ void k_expand_write(const float* __restrict__ pts, const float* __restrict__ rgb,
-                               const int32_t* __restrict__ accept, const int32_t* __restrict__ off, int64_t M,
-                               int64_t n_old, int K3, float logit, NewRows r) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= M || !accept[i]) return;
-  const int64_t g = n_old + off[i];
-  for (int k = 0; k < 3; ++k) r.means[3 * g + k] = pts[3 * i + k];
-  r.quats[4 * g] = 1.f;
-  r.quats[4 * g + 1] = r.quats[4 * g + 2] = r.quats[4 * g + 3] = 0.f;
-  r.opac[g] = logit;
-  float* f = r.sh + g * K3;
-  for (int k = 0; k < 3; ++k) f[k] = (rgb[3 * i + k] - 0.5f) / kY0;
-  for (int k = 3; k < K3; ++k) f[k] = 0.f;
-  const int len[5] = {3, 3, 4, 1, K3};
-  for (int a = 0; a < 5; ++a)
-    for (int k = 0; k < len[a]; ++k) {
-      r.m[a][g * len[a] + k] = 0.f;
-      r.v[a][g * len[a] + k] = 0.f;
-    }
+// Rows [0, m) of an array from row g0 on are zeroed, or set by f(row, element); contiguous over the block.
+template <class F>
+__device__ __forceinline__ void write_rows(float* __restrict__ a, int64_t g0, int m, int len, F f) {
+  a += g0 * len;
+  for (int e = threadIdx.x; e < m * len; e += 256) a[e] = f(e / len, e % len);
+}
+
+// A block's accepted points fill consecutive rows; it writes them array by array (a thread per point writing its own
+// rows made every store a line of its own).  blockIdx.y: parameters, first and second moments.
+__global__ __launch_bounds__(256) void k_expand_write(const float* __restrict__ pts, const float* __restrict__ rgb,
+                                                      const int32_t* __restrict__ accept,
+                                                      const int32_t* __restrict__ off, int64_t M, int64_t n_old, int K3,
+                                                      float logit, NewRows r) {
+  __shared__ int32_t src[256];
+  const int64_t i0 = (int64_t)blockIdx.x * 256, i = i0 + threadIdx.x, last = min(i0 + 256, M) - 1;
+  const int32_t first = off[i0];
+  const int m = off[last] + accept[last] - first;
+  const int64_t g0 = n_old + first;
+  if (blockIdx.y) {
+    float* const* d = blockIdx.y == 1 ? r.m : r.v;
+    const auto zero = [](int, int) { return 0.f; };
+    write_rows(d[0], g0, m, 3, zero);
+    write_rows(d[1], g0, m, 3, zero);
+    write_rows(d[2], g0, m, 4, zero);
+    write_rows(d[3], g0, m, 1, zero);
+    write_rows(d[4], g0, m, K3, zero);
+    return;
+  }
+  if (i < M && accept[i]) src[off[i] - first] = (int32_t)i;
+  __syncthreads();
+  write_rows(r.means, g0, m, 3, [&](int p, int k) { return pts[3 * (int64_t)src[p] + k]; });
+  write_rows(r.quats, g0, m, 4, [](int, int k) { return k == 0 ? 1.f : 0.f; });
+  write_rows(r.opac, g0, m, 1, [&](int, int) { return logit; });
+  write_rows(r.sh, g0, m, K3, [&](int p, int k) { return k < 3 ? (rgb[3 * (int64_t)src[p] + k] - 0.5f) / kY0 : 0.f; });
 }
 
 }  // namespace
 
 namespace gs_launch {
 
-// Scratch layout (int32 units, 64-aligned pieces): point keys/vals x2, map keys/vals x2, accept, off, brute list,
-// counters, sort scratch (reused by the three sorts), scan scratch.
+// Scratch layout (int32 units, 64-aligned pieces): point keys/vals x2, sorted positions, accept, off, brute list (before
+// it the map's counts per voxel), counters, sort scratch (reused by the two sorts), scan scratch.
 struct ExpandLayout {
-  size_t pk0, pk1, pv0, pv1, mk0, mk1, mv0, mv1, acc, off, brute, cnt, sort, scan, total;
+  size_t pk0, pk1, pv0, pv1, sp, acc, off, brute, cnt, sort, scan, total;
 };
 
 static size_t a64(size_t x) { return (x + 63) / 64 * 64; }
 
-static ExpandLayout expand_layout(int64_t N, int64_t M) {
+static ExpandLayout expand_layout(int64_t M) {
   ExpandLayout L;
   size_t o = 0;
-  const size_t m2 = a64(2 * (size_t)M), n2 = a64(2 * (size_t)(N > 0 ? N : 1));
+  const size_t m2 = a64(2 * (size_t)M);
   L.pk0 = o; o += m2; L.pk1 = o; o += m2; L.pv0 = o; o += a64(M); L.pv1 = o; o += a64(M);
-  L.mk0 = o; o += n2; L.mk1 = o; o += n2; L.mv0 = o; o += a64(N > 0 ? N : 1); L.mv1 = o; o += a64(N > 0 ? N : 1);
+  L.sp = o; o += a64(4 * (size_t)M + 4);  // (room to start at a multiple of 16 bytes)
   L.acc = o; o += a64(M); L.off = o; o += a64(M); L.brute = o; o += a64(M); L.cnt = o; o += 64;
-  const int64_t big = M > N ? M : N;
-  L.sort = o; o += a64(sort_scratch_ints(big > 0 ? big : 1));
+  L.sort = o; o += a64(sort_scratch_ints(M > 0 ? M : 1));
   L.scan = o; o += a64(scan_scratch_ints(M > 0 ? M : 1));
   L.total = o;
   return L;
 }
 
-size_t expand_scratch_ints(int64_t n_old, int64_t M) { return expand_layout(n_old, M).total; }
+size_t expand_scratch_ints(int64_t M) { return expand_layout(M).total; }
 
 hipError_t expand(const gs_params& p, const gs_params& m, const gs_params& v, int64_t n_old, const float* pts,
                   const float* rgb, int64_t M, const gs_camera& cam, const float* vis, float tau, float near_z,
                   float voxel, int cap, float cell, float init_logit, int64_t* n_added, int32_t* scratch,
                   hipStream_t st) {
-  const ExpandLayout L = expand_layout(n_old, M);
+  const ExpandLayout L = expand_layout(M);
   auto u64 = [&](size_t o) { return reinterpret_cast<uint64_t*>(scratch + o); };
   int32_t* cnt = scratch + L.cnt;
   hipError_t e = fill_i32(cnt, 0, 64, st);
@@ -289,7 +365,9 @@ hipError_t expand(const gs_params& p, const gs_params& m, const gs_params& v, in
   for (int k = 0; k < 9; ++k) c.R[k] = cam.R[k];
   for (int k = 0; k < 3; ++k) c.T[k] = cam.T[k];
   c.fx = cam.fx; c.fy = cam.fy; c.cx = cam.cx; c.cy = cam.cy; c.W = cam.width; c.H = cam.height;
-  const unsigned bm = (unsigned)((M + 255) / 256), bn = (unsigned)((n_old + 255) / 256);
+  const unsigned bm = (unsigned)((M + 255) / 256);
+  int32_t* have = scratch + L.brute;
+  if ((e = fill_i32(have, 0, M, st)) != hipSuccess) return e;
   // 1. filter + voxel keys, sorted (stable: input order inside a voxel)
   k_point_keys<<<bm, 256, 0, st>>>(pts, M, c, vis, tau, near_z, voxel, u64(L.pk0), scratch + L.pv0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -297,14 +375,12 @@ hipError_t expand(const gs_params& p, const gs_params& m, const gs_params& v, in
                       scratch + L.sort, st)) != hipSuccess)
     return e;  // 8 passes: the sorted pairs are back in the first buffers
   if (n_old > 0) {
-    k_map_keys<<<bn, 256, 0, st>>>(p.means, n_old, voxel, u64(L.mk0), scratch + L.mv0);
+    const int64_t bn = (n_old + 255) / 256;
+    k_map_count<<<(unsigned)(bn < 2048 ? bn : 2048), 256, 0, st>>>(p.means, n_old, voxel, u64(L.pk0), (int)M, cap, have);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = sort_pairs(u64(L.mk0), scratch + L.mv0, u64(L.mk1), scratch + L.mv1, n_old, nullptr, n_old, 64,
-                        scratch + L.sort, st)) != hipSuccess)
-      return e;
   }
   // 2. acceptance, and the output order
-  k_accept<<<bm, 256, 0, st>>>(u64(L.pk0), scratch + L.pv0, M, u64(L.mk0), n_old, cap, scratch + L.acc);
+  k_accept<<<bm, 256, 0, st>>>(u64(L.pk0), scratch + L.pv0, M, have, cap, scratch + L.acc);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = scan_exclusive(scratch + L.acc, scratch + L.off, M, scratch + L.scan, st)) != hipSuccess) return e;
   k_accept_total<<<1, 64, 0, st>>>(scratch + L.acc, scratch + L.off, M, cnt, n_added);
@@ -316,10 +392,13 @@ hipError_t expand(const gs_params& p, const gs_params& m, const gs_params& v, in
                       st)) != hipSuccess)
     return e;
   float* ls_new = p.log_scales + 3 * n_old;
-  k_knn<<<bm, 256, 0, st>>>(pts, u64(L.pk1), scratch + L.pv1, cnt, cell, scratch + L.off, ls_new,
-                            scratch + L.brute, cnt + 1);
+  auto* sp = reinterpret_cast<float4*>((reinterpret_cast<uintptr_t>(scratch + L.sp) + 15) & ~(uintptr_t)15);
+  k_sorted_points<<<bm, 256, 0, st>>>(pts, scratch + L.pv1, cnt, sp);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_knn_brute<<<256, 256, 0, st>>>(pts, scratch + L.pv1, cnt, scratch + L.brute, cnt + 1, scratch + L.off, ls_new);
+  k_knn<<<(unsigned)((M * kKnnLanes + 255) / 256), 256, 0, st>>>(sp, u64(L.pk1), cnt, cell, scratch + L.off, ls_new,
+                                                                 scratch + L.brute, cnt + 1);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  k_knn_brute<<<256, 256, 0, st>>>(sp, cnt, scratch + L.brute, cnt + 1, scratch + L.off, ls_new);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   NewRows r;
   r.means = p.means; r.quats = p.quats; r.opac = p.opacity; r.sh = p.sh;
@@ -329,7 +408,7 @@ hipError_t expand(const gs_params& p, const gs_params& m, const gs_params& v, in
     d[0] = mv[k]->means; d[1] = mv[k]->log_scales; d[2] = mv[k]->quats; d[3] = mv[k]->opacity; d[4] = mv[k]->sh;
   }
   const int K3 = 3 * (p.sh_degree + 1) * (p.sh_degree + 1);
-  k_expand_write<<<bm, 256, 0, st>>>(pts, rgb, scratch + L.acc, scratch + L.off, M, n_old, K3, init_logit, r);
+  k_expand_write<<<dim3(bm, 3), 256, 0, st>>>(pts, rgb, scratch + L.acc, scratch + L.off, M, n_old, K3, init_logit, r);
   return hipGetLastError();
 }
 
