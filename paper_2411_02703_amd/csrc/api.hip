@@ -125,7 +125,7 @@ Layout make_layout(int64_t n, int V, int n_tiles, int64_t cap, const gs_opts* op
   L.v1 = take((size_t)cap * 4);
   L.range = take((size_t)n_tiles * 8);
   L.order = take((size_t)n_tiles * 4);
-  L.counters = take(256 * 4);
+  L.counters = take(gs_launch::counter_ints() * 4);
   L.loss = take(64 * 4);
   L.segcount = take((size_t)n_tiles * 4);
   L.segfirst = take((size_t)n_tiles * 4);
@@ -139,7 +139,7 @@ Layout make_layout(int64_t n, int V, int n_tiles, int64_t cap, const gs_opts* op
   // (the per-Gaussian count scans run as one pair: twice a scan's scratch over n)
   size_t s1 = gs_launch::scan_scratch_ints(big);
   if (2 * gs_launch::scan_scratch_ints(n) > s1) s1 = 2 * gs_launch::scan_scratch_ints(n);
-  const size_t s2 = gs_launch::sort_scratch_ints(cap);
+  const size_t s2 = gs_launch::frame_sort_scratch_ints(cap);
   L.scratch_ints = s1 > s2 ? s1 : s2;
   L.scratch = take(L.scratch_ints * 4);
   L.total = o;
@@ -356,11 +356,7 @@ int gs_bin_tiles(const gs_frame* f, const gs_opts* o, int32_t sync_count, int64_
     count_dev = nullptr;
   }
   GS_HIP(gs_launch::emit(*f, n_sized, st), "gs_bin_tiles: emit");
-  // the instance sort folds its histogram scans only for small frames (a few M instances): with ~20 M the
-  // scatter's extra scan costs more than the launch it saves (measured)
-  GS_HIP(gs_launch::sort_pairs32(f->keys[0], f->vals[0], f->keys[1], f->vals[1], n_sized, count_dev, f->capacity,
-                                 f->key_bits, f->scratch, st, 256),
-         "gs_bin_tiles: sort by tile");
+  GS_HIP(gs_launch::sort_by_tile(*f, n_sized, count_dev, st), "gs_bin_tiles: sort by tile");
   GS_HIP(gs_launch::ranges(*f, f->keys[f->sort_passes & 1], n_sized, count_dev, st), "gs_bin_tiles: ranges");
   GS_HIP(gs_launch::tile_schedule(*f, st), "gs_bin_tiles: schedule");
   GS_HIP(gs_launch::work_items(*f, st), "gs_bin_tiles: work items");

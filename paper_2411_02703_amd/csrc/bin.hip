@@ -20,11 +20,6 @@ constexpr int kScanThreads = 256;
 constexpr int kScanItems = 16;
 constexpr int kScanTile = kScanThreads * kScanItems;  // 4096
 
-constexpr int kSortThreads = 256;
-constexpr int kSortItems = 8;
-constexpr int kSortTile = kSortThreads * kSortItems;  // 2048 keys per block
-constexpr int kWaveItems = kSortTile / 4;              // 512 keys per wave
-
 // Exclusive scan of 256 values, one per thread; returns the exclusive prefix, *total = sum.
 __device__ __forceinline__ int block_scan_256(int x, int* sh_wave, int* total) {
   const int lane = __lane_id(), wave = threadIdx.x >> 6;
@@ -145,85 +140,135 @@ __device__ __forceinline__ int64_t sort_count(const int32_t* count_dev, int64_t 
   return c < cap ? c : cap;
 }
 
-template <class KeyT>
-__global__ __launch_bounds__(kSortThreads) void k_sort_hist(const KeyT* __restrict__ keys,
-                                                           const int32_t* __restrict__ count_dev, int64_t n_sized,
-                                                           int64_t cap, int shift, int32_t* __restrict__ hist) {
-  __shared__ int h[256];
-  const int64_t n = sort_count(count_dev, n_sized, cap);
-  // digit-major histogram over the blocks that hold keys: hist[d * nb + b]
-  const int nb = (int)((n + kSortTile - 1) / kSortTile);
-  if ((int)blockIdx.x >= nb) return;
-  h[threadIdx.x] = 0;
-  __syncthreads();
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  for (int i = 0; i < kSortItems; ++i) {
-    const int64_t idx = base + i * kSortThreads + threadIdx.x;
-    if (idx < n) atomicAdd(&h[(int)((keys[idx] >> shift) & 255u)], 1);
-  }
-  __syncthreads();
-  hist[threadIdx.x * nb + blockIdx.x] = h[threadIdx.x];
+// Radix sort, one launch per 8-bit digit: k_sort_digits counts every digit of every key in one read; each pass then
+// finds its blocks' positions by a chained scan (a block publishes its digit counts, adds up those of the blocks before
+// it and publishes the sums).  With a histogram pass and a scan pass per digit in place of the chain, which cost two
+// launches and a read of the keys each, the six passes of a keyframe step (0.75 M records, 1.5 M instances) took 234 us
+// and those of a 24-view step (3.3 M and 21.6 M) 730; now 180 and 491, 21 and 67 of them for the digits.
+//
+// Words of a sort that must be zero before its first launch: digit counts and a ticket per pass.  The counts are kept
+// in kCopies copies, since the blocks' adds to one cache line queue (about 5 ns each).
+constexpr int kCopies = 8;
+constexpr int kSortZero32 = kCopies * 4 * 256 + 64, kSortZero64 = kCopies * 8 * 256 + 64;
+
+// A tile's state for one digit: 0 so far absent, 1 + the count of its keys, or with the top bit the count of its and all
+// earlier tiles' keys (below 2^31, as the sizes are).  Written and read whole, so that no other ordering is needed.
+constexpr uint32_t kWhole = 0x80000000u;
+__device__ __forceinline__ void put_state(uint32_t* p, uint32_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t get_state(const uint32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Stable scatter of one 8-bit digit.  Each wave ranks its 512 keys (8 rounds of 64) with ballot-based
-// digit matching, the block orders them in LDS (digit-major, stable), then writes runs to their global
-// offsets from the scanned digit-major histogram (entry d * nb + b over the nb blocks that hold keys: the
-// tile-local scan hist_scan plus the scanned total of its scan tile, tile_scan).
-// Histogram scans of at most this many tiles can be finished inside the scatter (each block scans the tile
-// totals itself, four per thread); whether they are is the caller's choice (fold_tiles), since with many keys
-// per pass the scatter's extra phase costs more than the separate pass it saves.
-constexpr int kFoldTiles = 4 * kSortThreads;
+constexpr int kDigitThreads = 256;
+constexpr int kDigitItems = 8;
+constexpr int kDigitBlocks = 1024;
 
-template <class KeyT, bool FOLD>
-__global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const KeyT* __restrict__ kin,
-                                                              const int32_t* __restrict__ vin,
-                                                              KeyT* __restrict__ kout, int32_t* __restrict__ vout,
-                                                              const int32_t* __restrict__ count_dev, int64_t n_sized,
-                                                              int64_t cap, int shift,
-                                                              const int32_t* __restrict__ hist_scan,
-                                                              const int32_t* __restrict__ tile_scan) {
-  __shared__ KeyT sk[kSortTile];
-  __shared__ int32_t sv[kSortTile];
-  __shared__ int32_t wcnt[4][256];
-  __shared__ int32_t dstart[256];
-  __shared__ int32_t gofs[256];
-  __shared__ int sh_wave[4];
-  __shared__ int32_t tsc[FOLD ? kFoldTiles : 1];
+// Keys per tile of the passes, by the number of keys (known on the device only).  Small sorts want many short blocks,
+// large ones long runs in the output and few states: with 2048 and 8192 keys a tile a pass of 2 k keys takes 5.2 and
+// 9.7 us, of 100 k 64-bit keys 7.3 and 11.9, of 270 k 22.8 and 21.3, of 0.75 M 39 and 30, of 1.5 M 52 and 40.
+constexpr int kSortThreads = 1024;
+constexpr int kSmallItems = 2, kLargeItems = 8;
+constexpr int64_t kSmallSort = int64_t(1) << 19;
+__host__ __device__ inline int sort_tile(int64_t n) {
+  return kSortThreads * (n <= kSmallSort ? kSmallItems : kLargeItems);
+}
+
+// (The first pass's states are cleared here.)
+template <class KeyT>
+__global__ __launch_bounds__(kDigitThreads) void k_sort_digits(const KeyT* __restrict__ keys,
+                                                               const int32_t* __restrict__ count_dev, int64_t n_sized,
+                                                               int64_t cap, int passes,
+                                                               int32_t* __restrict__ digits,
+                                                               uint32_t* __restrict__ state) {
+  __shared__ int h[(int)sizeof(KeyT)][256];
   const int64_t n = sort_count(count_dev, n_sized, cap);
-  const int64_t base = (int64_t)blockIdx.x * kSortTile;
-  if (base >= n) return;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = __lane_id();
-  for (int w = 0; w < 4; ++w) wcnt[w][tid] = 0;
-  if (FOLD) {
-    // tile_scan holds the scan tiles' raw totals: every block forms their exclusive scan itself (at most
-    // kFoldTiles values, four per thread), in place of a separate pass over them
-    const int nbt = (int)((256 * ((n + kSortTile - 1) / kSortTile) + kScanTile - 1) / kScanTile);
-    int t[4], sum = 0;
+  const int tile = sort_tile(n);
+  const int64_t words = (n + tile - 1) / tile * 256;
+  for (int64_t i = (int64_t)blockIdx.x * kDigitThreads + threadIdx.x; i < words; i += (int64_t)gridDim.x * kDigitThreads)
+    state[i] = 0;
+  constexpr int kStep = kDigitThreads * kDigitItems;
+  if ((int64_t)blockIdx.x * kStep >= n) return;
+  for (int p = 0; p < passes; ++p) h[p][threadIdx.x] = 0;
+  __syncthreads();
+  for (int64_t base = (int64_t)blockIdx.x * kStep; base < n; base += (int64_t)gridDim.x * kStep) {
+    KeyT key[kDigitItems];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int idx = 4 * tid + i;
-      t[i] = idx < nbt ? tile_scan[idx] : 0;
-      sum += t[i];
+    for (int i = 0; i < kDigitItems; ++i) {
+      const int64_t idx = base + i * kDigitThreads + threadIdx.x;
+      key[i] = idx < n ? keys[idx] : KeyT(0);
     }
-    int total;
-    int run = block_scan_256(sum, sh_wave, &total);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      tsc[4 * tid + i] = run;
-      run += t[i];
+    for (int i = 0; i < kDigitItems; ++i) {
+      const bool valid = base + i * kDigitThreads + threadIdx.x < n;
+      const uint64_t vb = __ballot(valid);
+      if (vb == 0) break;
+      const int lead = __builtin_ctzll(vb);
+      for (int p = 0; p < passes; ++p) {
+        // the first lane's digit is counted once for the wave: high digits agree in most lanes, and adds of many
+        // lanes to one address are taken one by one
+        const int d = (int)((key[i] >> (8 * p)) & 255u);
+        const int d0 = __builtin_amdgcn_readlane(d, lead);
+        const uint64_t same = __ballot(valid && d == d0);
+        if (valid && d != d0) atomicAdd(&h[p][d], 1);
+        if ((int)__lane_id() == lead) atomicAdd(&h[p][d0], (int)__popcll(same));
+      }
     }
   }
   __syncthreads();
-  KeyT key[kSortItems];
-  int32_t val[kSortItems];
-  int pos[kSortItems];
+  for (int p = 0; p < passes; ++p) {
+    const int c = h[p][threadIdx.x];
+    if (c) atomicAdd(digits + 256 * ((blockIdx.x % kCopies) * passes + p) + threadIdx.x, c);
+  }
+}
+
+// Stable scatter of one 8-bit digit.  Tiles are taken in the order of a ticket counter, so that every tile before a
+// running block's belongs to a block that runs or has finished: the waits below end, because a block publishes its own
+// counts before it waits.  Each wave ranks its keys (ITEMS rounds of 64) with ballot-based digit matching, the block
+// orders them in LDS (digit-major, stable), adds up the earlier tiles' counts (a digit per thread, kLook tiles' words in
+// flight) and writes runs to their global places, first keys, then values through the same LDS.  state: this pass's
+// states, cleared before; next: the following pass's, cleared here.
+constexpr int kLook = 8;
+
+template <class KeyT>
+struct SortStage {
+  KeyT key[kSortThreads * kLargeItems];
+  uint16_t cnt[kSortThreads / 64][256];
+  int32_t ofs[256];
+  int wave[2][4];
+  int tile;
+};
+
+template <class KeyT, int ITEMS>
+__device__ __forceinline__ void scatter_tile(SortStage<KeyT>& s, const KeyT* __restrict__ kin,
+                                             const int32_t* __restrict__ vin, KeyT* __restrict__ kout,
+                                             int32_t* __restrict__ vout, int64_t n, int pass, int dc, uint32_t* state,
+                                             uint32_t* next) {
+  constexpr int THREADS = kSortThreads, TILE = THREADS * ITEMS, WAVES = THREADS / 64;
+  KeyT* sk = s.key;
+  int32_t* sv = reinterpret_cast<int32_t*>(s.key);
+  auto& wcnt = s.cnt;
+  auto& gofs = s.ofs;
+  auto& sh_wave = s.wave;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = __lane_id(), shift = 8 * pass;
+  const int tile = s.tile;
+  const int64_t base = (int64_t)tile * TILE;
+  const int nvalid = (int)min((int64_t)TILE, n - base);
+  kin += base;
+  vin += base;
+  const int i0 = wave * 64 * ITEMS + lane;
+  KeyT key[ITEMS];
+  int pos[ITEMS];
   const uint64_t lt = gsk::lanemask_lt();
 #pragma unroll
-  for (int k = 0; k < kSortItems; ++k) {
-    const int64_t idx = base + (int64_t)wave * kWaveItems + k * 64 + lane;
-    const bool valid = idx < n;
-    key[k] = valid ? kin[idx] : KeyT(0);
-    val[k] = valid ? vin[idx] : 0;
+  for (int k = 0; k < ITEMS; ++k) {
+    const bool valid = i0 + k * 64 < nvalid;
+    key[k] = valid ? kin[i0 + k * 64] : KeyT(0);
+  }
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const bool valid = i0 + k * 64 < nvalid;
     const int d = (int)((key[k] >> shift) & 255u);
     uint64_t peers = __ballot(valid);
 #pragma unroll
@@ -237,43 +282,114 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_scatter(const KeyT* __res
     if (valid) before = wcnt[wave][d];
     pos[k] = before + rank;
     __builtin_amdgcn_wave_barrier();
-    if (valid && rank == 0) wcnt[wave][d] = before + __popcll(peers);
+    if (valid && rank == 0) wcnt[wave][d] = (uint16_t)(before + __popcll(peers));
     __builtin_amdgcn_wave_barrier();
   }
   __syncthreads();
-  {
-    const int c0 = wcnt[0][tid], c1 = wcnt[1][tid], c2 = wcnt[2][tid], c3 = wcnt[3][tid];
-    int total;
-    const int ds = block_scan_256(c0 + c1 + c2 + c3, sh_wave, &total);
-    dstart[tid] = ds;
-    wcnt[0][tid] = ds;
-    wcnt[1][tid] = ds + c0;
-    wcnt[2][tid] = ds + c0 + c1;
-    wcnt[3][tid] = ds + c0 + c1 + c2;
-    const int hi = tid * (int)((n + kSortTile - 1) / kSortTile) + blockIdx.x;
-    gofs[tid] = hist_scan[hi] + (FOLD ? tsc[hi / kScanTile] : tile_scan[hi / kScanTile]);
+  // digit tid: the tile's count is published, the waves' first places in the tile and the digit's first place overall
+  uint32_t* my_state = state + (int64_t)tile * 256 + tid;
+  int total = 0, in_c = 0, in_d = 0;
+  if (tid < 256) {
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) total += wcnt[w][tid];
+    put_state(my_state, tile == 0 ? kWhole | (uint32_t)total : (uint32_t)total + 1u);
+    next[(int64_t)tile * 256 + tid] = 0;
+    int t;
+    in_c = gsk::wave_excl_scan(total, t);
+    if (lane == 0) sh_wave[0][wave] = t;
+    in_d = gsk::wave_excl_scan(dc, t);
+    if (lane == 0) sh_wave[1][wave] = t;
   }
   __syncthreads();
+  if (tid < 256) {
+    for (int w = 0; w < wave; ++w) {
+      in_c += sh_wave[0][w];
+      in_d += sh_wave[1][w];
+    }
+    int run = in_c;
 #pragma unroll
-  for (int k = 0; k < kSortItems; ++k) {
-    const int64_t idx = base + (int64_t)wave * kWaveItems + k * 64 + lane;
-    if (idx < n) {
-      const int d = (int)((key[k] >> shift) & 255u);
-      const int p = wcnt[wave][d] + pos[k];
-      sk[p] = key[k];
-      sv[p] = val[k];
+    for (int w = 0; w < WAVES; ++w) {
+      const int c = wcnt[w][tid];
+      wcnt[w][tid] = (uint16_t)run;
+      run += c;
     }
   }
   __syncthreads();
-  const int64_t rem = n - base;
-  const int nvalid = rem < kSortTile ? (int)rem : kSortTile;
-  for (int p = tid; p < nvalid; p += kSortThreads) {
-    const KeyT kk = sk[p];
-    const int d = (int)((kk >> shift) & 255u);
-    const int64_t o = (int64_t)gofs[d] + (p - dstart[d]);
-    kout[o] = kk;
-    vout[o] = sv[p];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    if (i0 + k * 64 < nvalid) {
+      pos[k] += wcnt[wave][(int)((key[k] >> shift) & 255u)];
+      sk[pos[k]] = key[k];
+    }
   }
+  int32_t val[ITEMS];  // (here, so that the loads' time passes in the waits below)
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) val[k] = i0 + k * 64 < nvalid ? vin[i0 + k * 64] : 0;
+  if (tid < 256) {
+    uint32_t before = 0;
+    if (tile > 0) {
+      for (int j = tile - 1;;) {
+        uint32_t v[kLook];
+#pragma unroll
+        for (int i = 0; i < kLook; ++i) v[i] = get_state(state + (int64_t)max(j - i, 0) * 256 + tid);
+        bool done = false;
+#pragma unroll
+        for (int i = 0; i < kLook; ++i) {
+          if (done || v[i] == 0) break;  // (absent so far: read again from here)
+          done = (v[i] & kWhole) != 0;
+          before += done ? v[i] & ~kWhole : v[i] - 1u;
+          --j;
+        }
+        if (done) break;
+      }
+      put_state(my_state, kWhole | (before + (uint32_t)total));
+    }
+    gofs[tid] = in_d + (int)before - in_c;
+  }
+  __syncthreads();
+  int out[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int p = k * THREADS + tid;
+    if (p < nvalid) {
+      const KeyT kk = sk[p];
+      out[k] = gofs[(int)((kk >> shift) & 255u)] + p;
+      kout[out[k]] = kk;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k)
+    if (i0 + k * 64 < nvalid) sv[pos[k]] = val[k];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const int p = k * THREADS + tid;
+    if (p < nvalid) vout[out[k]] = sv[p];
+  }
+}
+
+template <class KeyT>
+__global__ __launch_bounds__(kSortThreads, sizeof(KeyT) == 4 ? 8 : 4) void k_sort_scatter(
+    const KeyT* __restrict__ kin, const int32_t* __restrict__ vin, KeyT* __restrict__ kout, int32_t* __restrict__ vout,
+    const int32_t* __restrict__ count_dev, int64_t n_sized, int64_t cap, int pass, int passes, int32_t* digits,
+    uint32_t* state, uint32_t* next) {
+  __shared__ SortStage<KeyT> s;
+  const int64_t n = sort_count(count_dev, n_sized, cap);
+  if ((int64_t)blockIdx.x * sort_tile(n) >= n) return;  // (as many blocks as tiles go on)
+  const int tid = threadIdx.x;
+  if (tid == 0) s.tile = atomicAdd(digits + kCopies * 256 * passes + pass, 1);
+  for (int i = tid; i < kSortThreads / 64 * 256; i += kSortThreads) (&s.cnt[0][0])[i] = 0;
+  int dc = 0;  // the digit's keys
+  if (tid < 256) {
+#pragma unroll
+    for (int i = 0; i < kCopies; ++i) dc += digits[256 * (i * passes + pass) + tid];
+  }
+  __syncthreads();
+  if (n <= kSmallSort)
+    scatter_tile<KeyT, kSmallItems>(s, kin, vin, kout, vout, n, pass, dc, state, next);
+  else
+    scatter_tile<KeyT, kLargeItems>(s, kin, vin, kout, vout, n, pass, dc, state, next);
 }
 
 // ------------------------------------------------------------------ the record list and the emission
@@ -295,6 +411,7 @@ __device__ __forceinline__ int rect_area(const short4 rc) { return (rc.y - rc.x 
 // to big_rec (count in counters[kBigCount], one atomic per wave; the list order is not fixed, which nothing
 // depends on).
 constexpr int kBigCount = 198;
+constexpr int kFrameCounters = 256;  // the frame's counters; behind them the two sorts' zeroed words
 
 __global__ __launch_bounds__(256) void k_record_list(const uint64_t* __restrict__ vis_mask,
                                                     const int32_t* __restrict__ n_rec,
@@ -713,19 +830,6 @@ static hipError_t scan_exclusive_pair(const int32_t* in0, int32_t* out0, const i
   return hipGetLastError();
 }
 
-// The first two phases of scan_exclusive: out holds each kScanTile tile's exclusive scan and scratch[0 ..) the
-// exclusive scan of the tile totals, so the exclusive scan at i is out[i] + scratch[i / kScanTile] (for a
-// consumer that reads each entry once, in place of the pass that would add them).
-static hipError_t scan_exclusive_tiles(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t st,
-                                       DevCount dc) {
-  if (n <= 0) return hipSuccess;
-  const int64_t nb = cdiv(n, kScanTile);
-  k_scan_tile<<<(unsigned)nb, kScanThreads, 0, st>>>(in, out, n, scratch, dc);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  return scan_exclusive(scratch, scratch, nb, scratch + align64(nb), st, DevCount{});
-}
-
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   k_fill_i32<<<(unsigned)cdiv(n, 256), 256, 0, st>>>(p, v, n);
@@ -738,67 +842,63 @@ hipError_t fill_f32(float* p, float v, int64_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-size_t sort_scratch_ints(int64_t n) {
-  const int64_t nb = cdiv(n > 0 ? n : 1, kSortTile);
-  return (size_t)align64(256 * nb) + scan_scratch_ints(256 * nb);
+// Tiles of a sort of up to n keys, and its two passes' states.
+static int64_t sort_blocks(int64_t n) {
+  if (n < 1) n = 1;
+  const int64_t few = n < kSmallSort ? n : kSmallSort;
+  const int64_t small = cdiv(few, sort_tile(few)), large = cdiv(n, sort_tile(n));
+  return small > large ? small : large;
 }
+static size_t state_ints(int64_t n) { return 512 * (size_t)sort_blocks(n); }
 
+size_t sort_scratch_ints(int64_t n) { return (size_t)kSortZero64 + state_ints(n); }
+size_t frame_sort_scratch_ints(int64_t n) { return state_ints(n); }
+
+// zeroed: the words described at kSortZero32 / 64, zero; states: state_ints(n_sized).
 template <class KeyT>
 static hipError_t sort_impl(KeyT* k0, int32_t* v0, KeyT* k1, int32_t* v1, int64_t n_sized, const int32_t* count_dev,
-                            int64_t cap, int key_bits, int32_t* scratch, hipStream_t st, int fold_tiles) {
+                            int64_t cap, int key_bits, int32_t* zeroed, int32_t* states, hipStream_t st) {
   if (n_sized <= 0) return hipSuccess;
-  const int64_t nb = cdiv(n_sized, kSortTile);
-  int32_t* hist = scratch;
-  int32_t* scan_scr = scratch + align64(256 * nb);
+  const int64_t nb = sort_blocks(n_sized);
   const int passes = (key_bits + 7) / 8;
+  uint32_t* state[2] = {reinterpret_cast<uint32_t*>(states), reinterpret_cast<uint32_t*>(states) + 256 * nb};
+  const int64_t db = cdiv(n_sized, kDigitThreads * kDigitItems);
+  k_sort_digits<KeyT><<<(unsigned)(db < kDigitBlocks ? db : kDigitBlocks), kDigitThreads, 0, st>>>(
+      k0, count_dev, n_sized, cap, passes, zeroed, state[0]);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
   KeyT* kb[2] = {k0, k1};
   int32_t* vb[2] = {v0, v1};
   for (int p = 0; p < passes; ++p) {
-    const int shift = 8 * p;
     const int src = p & 1, dst = src ^ 1;
-    k_sort_hist<KeyT><<<(unsigned)nb, kSortThreads, 0, st>>>(kb[src], count_dev, n_sized, cap, shift, hist);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    // the histogram holds 256 * cdiv(count, kSortTile) entries; the scatter adds the scanned tile totals itself
-    // (and, for at most kFoldTiles scan tiles, scans those totals itself too)
-    const DevCount dc{count_dev, cap, kSortTile, 256};
-    if (cdiv(256 * nb, kScanTile) <= fold_tiles) {
-      k_scan_tile<<<(unsigned)cdiv(256 * nb, kScanTile), kScanThreads, 0, st>>>(hist, hist, 256 * nb, scan_scr, dc);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-      k_sort_scatter<KeyT, true><<<(unsigned)nb, kSortThreads, 0, st>>>(kb[src], vb[src], kb[dst], vb[dst],
-                                                                        count_dev, n_sized, cap, shift, hist,
-                                                                        scan_scr);
-    } else {
-      e = scan_exclusive_tiles(hist, hist, 256 * nb, scan_scr, st, dc);
-      if (e != hipSuccess) return e;
-      k_sort_scatter<KeyT, false><<<(unsigned)nb, kSortThreads, 0, st>>>(kb[src], vb[src], kb[dst], vb[dst],
-                                                                         count_dev, n_sized, cap, shift, hist,
-                                                                         scan_scr);
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    k_sort_scatter<KeyT><<<(unsigned)nb, kSortThreads, 0, st>>>(kb[src], vb[src], kb[dst], vb[dst], count_dev, n_sized,
+                                                                cap, p, passes, zeroed, state[src], state[dst]);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
 hipError_t sort_pairs(uint64_t* k0, int32_t* v0, uint64_t* k1, int32_t* v1, int64_t n_sized, const int32_t* count_dev,
                       int64_t cap, int key_bits, int32_t* scratch, hipStream_t st) {
-  return sort_impl<uint64_t>(k0, v0, k1, v1, n_sized, count_dev, cap, key_bits, scratch, st, kFoldTiles);
+  hipError_t e = fill_i32(scratch, 0, kSortZero64, st);
+  if (e != hipSuccess) return e;
+  return sort_impl<uint64_t>(k0, v0, k1, v1, n_sized, count_dev, cap, key_bits, scratch, scratch + kSortZero64, st);
 }
 
-hipError_t sort_pairs32(uint32_t* k0, int32_t* v0, uint32_t* k1, int32_t* v1, int64_t n_sized,
-                        const int32_t* count_dev, int64_t cap, int key_bits, int32_t* scratch, hipStream_t st,
-                        int fold_tiles) {
-  return sort_impl<uint32_t>(k0, v0, k1, v1, n_sized, count_dev, cap, key_bits, scratch, st,
-                             fold_tiles < kFoldTiles ? fold_tiles : kFoldTiles);
+hipError_t sort_by_tile(const gs_frame& f, int64_t n_sized, const int32_t* count_dev, hipStream_t st) {
+  return sort_impl<uint32_t>(f.keys[0], f.vals[0], f.keys[1], f.vals[1], n_sized, count_dev, f.capacity, f.key_bits,
+                             f.counters + kFrameCounters + kSortZero32, f.scratch, st);
 }
+
+size_t counter_ints() { return kFrameCounters + 2 * (size_t)kSortZero32; }
 
 // Binning up to the instance total: the records' first partial slots, the record list sorted by depth (record ids
 // in rvals[0]), each sorted record's tile rectangle (rkeys[0], rkeys[1]) and first emission index (rvals[1]), the
 // instance total and the overflow flag.
 hipError_t bin_records(const gs_frame& f, hipStream_t st) {
   const int64_t rcap = f.rec_cap;
-  hipError_t e = fill_i32(f.counters + kInstSum, 0, 2, st);  // kInstSum, kBigCount
+  // kInstSum, kBigCount (and the unused counters) and the two sorts' words behind the counters
+  hipError_t e = fill_i32(f.counters + kInstSum, 0, (int64_t)counter_ints() - kInstSum, st);
   if (e != hipSuccess) return e;
   if ((e = scan_exclusive_pair(f.n_rec, f.rec_first, f.n_inst, f.inst_first, f.n, f.scratch, st)) != hipSuccess)
     return e;
@@ -807,8 +907,8 @@ hipError_t bin_records(const gs_frame& f, hipStream_t st) {
                                                           f.n, rcap, f.rkeys[0], f.rvals[0], f.rec_slot, f.big_rec,
                                                           f.counters, f.capacity);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = sort_pairs32(f.rkeys[0], f.rvals[0], f.rkeys[1], f.rvals[1], rcap, f.counters + kRecCount, rcap, 32,
-                        f.scratch, st, kFoldTiles)) != hipSuccess)
+  if ((e = sort_impl<uint32_t>(f.rkeys[0], f.rvals[0], f.rkeys[1], f.rvals[1], rcap, f.counters + kRecCount, rcap, 32,
+                               f.counters + kFrameCounters, f.scratch, st)) != hipSuccess)
     return e;  // 4 passes: the sorted records are back in rkeys[0] / rvals[0]
   // counts straight into rvals[1], scanned in place into the emission offsets; the sorted rectangles take the
   // depth keys' buffers, which are no longer needed
