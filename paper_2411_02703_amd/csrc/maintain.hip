@@ -45,12 +45,19 @@ Rows rows_of(const gs_params& p, const gs_params& m, const gs_params& v, const g
   return r;
 }
 
-// A block copies the rows src[0, m) (in LDS) of five arrays to the consecutive rows from row0 on, and blockIdx.y selects
+// A block copies the rows src[0, m) (in LDS, at most 256) of five arrays to the consecutive rows from row0 on, and blockIdx.y selects
 // parameters or moments.  What bounds it is HBM: reads and writes run element by element over the block's output, which
 // is contiguous, up to four loads a thread in flight, in 16-byte words where both arrays' rows are made of them.  The row
 // of a word is e / units by a multiplication (a 64-bit division per element had made the copy of 1M Gaussians of degree
 // 3 VALU-bound: 514 us pruned, 576 us permuted).
 constexpr int kRowBlock = 256;
+
+// Rows a block copies: some 4 k words of an array set, and few where there are few Gaussians.  Prune of 1M at 64, 128 and
+// 256 rows: degree 0 163, 129, 92 us; degree 2 217, 202, 208; degree 3 282, 297, 310; of 2000 of degree 3 18.3, 19.2,
+// 20.6 (the reorder's random reads hardly differ).
+inline int rows_per_block(int64_t n, int sh_degree) {
+  return n < (int64_t(1) << 14) || sh_degree >= 3 ? 64 : sh_degree == 2 ? 128 : 256;
+}
 
 template <int B, class T>
 __device__ __forceinline__ void copy_batch(const T* __restrict__ in, T* __restrict__ out, int e, int units, uint32_t inv,
@@ -94,13 +101,14 @@ __device__ __forceinline__ void copy_rows(const Rows& r, int64_t row0, int m, co
   }
 }
 
-// Block b lists the kept ones of its 256 Gaussians; their output rows are consecutive.
-__global__ __launch_bounds__(kRowBlock) void k_prune_gather(const Rows r, int64_t n, const int32_t* __restrict__ keep,
+// Block b lists the kept ones of its `rows` Gaussians; their output rows are consecutive.
+__global__ __launch_bounds__(kRowBlock) void k_prune_gather(const Rows r, int64_t n, int rows,
+                                                            const int32_t* __restrict__ keep,
                                                             const int32_t* __restrict__ off) {
   __shared__ int32_t src[kRowBlock];
-  const int64_t g0 = (int64_t)blockIdx.x * kRowBlock, g = g0 + threadIdx.x, last = min(g0 + kRowBlock, n) - 1;
+  const int64_t g0 = (int64_t)blockIdx.x * rows, g = g0 + threadIdx.x, last = min(g0 + rows, n) - 1;
   const int32_t row0 = off[g0];
-  if (g < n && keep[g]) src[off[g] - row0] = (int32_t)g;
+  if (g <= last && keep[g]) src[off[g] - row0] = (int32_t)g;
   __syncthreads();
   copy_rows(r, row0, off[last] + keep[last] - row0, src);
 }
@@ -125,7 +133,9 @@ hipError_t prune(const gs_params& p, const gs_params& m, const gs_params& v, flo
   if ((e = scan_exclusive(keep, off, n, scan_scr, st)) != hipSuccess) return e;
   k_prune_total<<<1, 64, 0, st>>>(keep, off, n, n_kept);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_prune_gather<<<dim3(blocks, 3), kRowBlock, 0, st>>>(rows_of(p, m, v, op, om, ov), n, keep, off);
+  const int rows = rows_per_block(n, p.sh_degree);
+  k_prune_gather<<<dim3((unsigned)((n + rows - 1) / rows), 3), kRowBlock, 0, st>>>(rows_of(p, m, v, op, om, ov), n, rows,
+                                                                                  keep, off);
   return hipGetLastError();
 }
 
@@ -209,10 +219,11 @@ __global__ void k_morton(const float* __restrict__ means, int64_t n, const uint3
 }
 
 // out row k = in row perm[k]
-__global__ __launch_bounds__(kRowBlock) void k_permute(const Rows r, int64_t n, const int32_t* __restrict__ perm) {
+__global__ __launch_bounds__(kRowBlock) void k_permute(const Rows r, int64_t n, int rows,
+                                                       const int32_t* __restrict__ perm) {
   __shared__ int32_t src[kRowBlock];
-  const int64_t k0 = (int64_t)blockIdx.x * kRowBlock;
-  const int m = (int)min((int64_t)kRowBlock, n - k0);
+  const int64_t k0 = (int64_t)blockIdx.x * rows;
+  const int m = (int)min((int64_t)rows, n - k0);
   if ((int)threadIdx.x < m) src[threadIdx.x] = perm[k0 + threadIdx.x];
   __syncthreads();
   copy_rows(r, k0, m, src);
@@ -249,8 +260,8 @@ hipError_t spatial_order(const gs_params& p, const gs_params& m, const gs_params
   k_morton<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(p.means, n, box, k0, v0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = sort_pairs(k0, v0, k1, v1, n, nullptr, n, 64, sort_scr, st)) != hipSuccess) return e;  // back in v0
-  k_permute<<<dim3((unsigned)((n + kRowBlock - 1) / kRowBlock), 3), kRowBlock, 0, st>>>(
-      rows_of(p, m, v, op, om, ov), n, v0);
+  const int rows = rows_per_block(n, p.sh_degree);
+  k_permute<<<dim3((unsigned)((n + rows - 1) / rows), 3), kRowBlock, 0, st>>>(rows_of(p, m, v, op, om, ov), n, rows, v0);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (perm_out) return hipMemcpyAsync(perm_out, v0, (size_t)n * 4, hipMemcpyDeviceToDevice, st);
   return hipSuccess;

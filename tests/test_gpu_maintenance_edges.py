@@ -26,7 +26,8 @@ def _set(n, deg, shift, rng=None):
 
 
 @pytest.mark.parametrize("shift_in,shift_out", [(0, 0), (1, 0), (0, 2), (3, 3)])
-@pytest.mark.parametrize("n,deg", [(1, 3), (255, 0), (256, 3), (257, 2), (511, 1), (140_001, 0), (5000, 3)])
+@pytest.mark.parametrize("n,deg", [(1, 3), (255, 0), (256, 3), (257, 2), (511, 1), (140_001, 0), (5000, 3),
+                                   (16_383, 0), (16_384, 1), (16_385, 2)])
 def test_pruned_and_reordered_rows_move_bit_for_bit(gpu_lib, n, deg, shift_in, shift_out):
     rng = np.random.default_rng(n + deg)
     sets = [_set(n, deg, shift_in, rng) for _ in range(3)]
