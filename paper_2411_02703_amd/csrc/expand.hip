@@ -131,20 +131,15 @@ __global__ void k_accept(const uint64_t* __restrict__ pk, const int32_t* __restr
   accept[pv[s]] = ok;
 }
 
-__global__ void k_accept_total(const int32_t* __restrict__ accept, const int32_t* __restrict__ off, int64_t M,
-                               int32_t* __restrict__ count, int64_t* __restrict__ n_added) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) {
-    const int32_t a = off[M - 1] + accept[M - 1];
-    count[0] = a;
-    n_added[0] = a;
-  }
-}
-
-// 3a. grid cell keys of the accepted points, compacted to their output order
+// 3a. grid cell keys of the accepted points, compacted to their output order, and their number
 __global__ void k_cell_keys(const float* __restrict__ pts, const int32_t* __restrict__ accept,
                             const int32_t* __restrict__ off, int64_t M, float cell, uint64_t* __restrict__ keys,
-                            int32_t* __restrict__ vals) {
+                            int32_t* __restrict__ vals, int32_t* __restrict__ count, int64_t* __restrict__ n_added) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i == M - 1) {
+    count[0] = off[i] + accept[i];
+    n_added[0] = count[0];
+  }
   if (i >= M || !accept[i]) return;
   int cc[3];
   const bool ok = cell_of(pts[3 * i], pts[3 * i + 1], pts[3 * i + 2], 0.f, cell, cc);
@@ -383,10 +378,9 @@ hipError_t expand(const gs_params& p, const gs_params& m, const gs_params& v, in
   k_accept<<<bm, 256, 0, st>>>(u64(L.pk0), scratch + L.pv0, M, have, cap, scratch + L.acc);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = scan_exclusive(scratch + L.acc, scratch + L.off, M, scratch + L.scan, st)) != hipSuccess) return e;
-  k_accept_total<<<1, 64, 0, st>>>(scratch + L.acc, scratch + L.off, M, cnt, n_added);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   // 3. cells of the accepted points (sorted, sized by M, counted on the device), spacing, the new rows
-  k_cell_keys<<<bm, 256, 0, st>>>(pts, scratch + L.acc, scratch + L.off, M, cell, u64(L.pk1), scratch + L.pv1);
+  k_cell_keys<<<bm, 256, 0, st>>>(pts, scratch + L.acc, scratch + L.off, M, cell, u64(L.pk1), scratch + L.pv1, cnt,
+                                  n_added);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = sort_pairs(u64(L.pk1), scratch + L.pv1, u64(L.pk0), scratch + L.pv0, M, cnt, M, 64, scratch + L.sort,
                       st)) != hipSuccess)

@@ -18,11 +18,6 @@ __global__ void k_prune_flags(const float* __restrict__ opac, int64_t n, float t
   if (i < n) keep[i] = opac[i] >= thr ? 1 : 0;
 }
 
-__global__ void k_prune_total(const int32_t* __restrict__ keep, const int32_t* __restrict__ off, int64_t n,
-                              int64_t* __restrict__ n_kept) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) n_kept[0] = (int64_t)off[n - 1] + keep[n - 1];
-}
-
 struct Rows {
   const float* in[15];
   float* out[15];
@@ -101,14 +96,16 @@ __device__ __forceinline__ void copy_rows(const Rows& r, int64_t row0, int m, co
   }
 }
 
-// Block b lists the kept ones of its `rows` Gaussians; their output rows are consecutive.
+// Block b lists the kept ones of its `rows` Gaussians; their output rows are consecutive.  The last one writes the total.
 __global__ __launch_bounds__(kRowBlock) void k_prune_gather(const Rows r, int64_t n, int rows,
                                                             const int32_t* __restrict__ keep,
-                                                            const int32_t* __restrict__ off) {
+                                                            const int32_t* __restrict__ off,
+                                                            int64_t* __restrict__ n_kept) {
   __shared__ int32_t src[kRowBlock];
   const int64_t g0 = (int64_t)blockIdx.x * rows, g = g0 + threadIdx.x, last = min(g0 + rows, n) - 1;
   const int32_t row0 = off[g0];
   if (g <= last && keep[g]) src[off[g] - row0] = (int32_t)g;
+  if (last == n - 1 && blockIdx.y == 0 && threadIdx.x == 0) n_kept[0] = (int64_t)off[last] + keep[last];
   __syncthreads();
   copy_rows(r, row0, off[last] + keep[last] - row0, src);
 }
@@ -131,11 +128,9 @@ hipError_t prune(const gs_params& p, const gs_params& m, const gs_params& v, flo
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if ((e = scan_exclusive(keep, off, n, scan_scr, st)) != hipSuccess) return e;
-  k_prune_total<<<1, 64, 0, st>>>(keep, off, n, n_kept);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
   const int rows = rows_per_block(n, p.sh_degree);
   k_prune_gather<<<dim3((unsigned)((n + rows - 1) / rows), 3), kRowBlock, 0, st>>>(rows_of(p, m, v, op, om, ov), n, rows,
-                                                                                  keep, off);
+                                                                                  keep, off, n_kept);
   return hipGetLastError();
 }
 
