@@ -167,8 +167,7 @@ typedef struct gs_frame {
   int64_t rec_cap;      /* capacity of the record list: min(n_views * n, capacity) */
   uint32_t* rkeys[2];   /* [rec_cap] record list: depth bits while sorting; then each sorted record's tile
                            rectangle, tx0 | tx1 << 16 in rkeys[0] and ty0 | ty1 << 16 in rkeys[1] */
-  int32_t* rvals[2];    /* [rec_cap] record list: record ids (sorted into rvals[0]); rvals[1] then holds each
-                           sorted record's first emission index */
+  int32_t* rvals[2];    /* [rec_cap] record list: record ids (sorted into rvals[0]; rvals[1] is sort scratch) */
   uint32_t* keys[2];    /* [capacity] instance keys: global tile ids (sorted into keys[sort_passes & 1]) */
   int32_t* vals[2];     /* [capacity] record id of each instance (sorted into vals[sort_passes & 1]; the other
                            buffer is sort scratch) */
@@ -178,7 +177,8 @@ typedef struct gs_frame {
                            [128..192) tile-length bucket counts and offsets, [192] work items,
                            [193] segment slots of split tiles, [194] split tiles, [196] visible records,
                            [197] instances summed per Gaussian, [198] records with more than 32 instances,
-                           [199..201] work-item counters of the persistent compositing launches */
+                           [199..201] work-item counters of the persistent compositing launches; behind them the
+                           sorts' digit counts and the totals that binning's running sums are formed from */
   int32_t* seg_count;   /* [n_tiles]: segments of the tile at each schedule position */
   int32_t* seg_first;   /* [n_tiles]: exclusive scan of seg_count = first work item of that tile */
   int32_t* items;       /* [item_cap][4]: work items of the compositing calls, split tiles first:
@@ -188,7 +188,7 @@ typedef struct gs_frame {
                            tiles; and behind it [n_tiles] each tile's loss */
   float* split;         /* [long_cap][12][tile_w * tile_h]: per-pixel stop state and upstream gradient */
   float* loss;          /* [64]: loss[0] the loss value written by gs_render_bwd in loss mode */
-  int32_t* scratch;     /* sort histograms and scan partials */
+  int32_t* scratch;     /* sort states and scan partials */
   size_t scratch_ints;
 } gs_frame;
 

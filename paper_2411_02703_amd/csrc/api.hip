@@ -125,7 +125,7 @@ Layout make_layout(int64_t n, int V, int n_tiles, int64_t cap, const gs_opts* op
   L.v1 = take((size_t)cap * 4);
   L.range = take((size_t)n_tiles * 8);
   L.order = take((size_t)n_tiles * 4);
-  L.counters = take(gs_launch::counter_ints() * 4);
+  L.counters = take(gs_launch::counter_ints(n, L.rec_cap) * 4);
   L.loss = take(64 * 4);
   L.segcount = take((size_t)n_tiles * 4);
   L.segfirst = take((size_t)n_tiles * 4);
@@ -136,9 +136,7 @@ Layout make_layout(int64_t n, int V, int n_tiles, int64_t cap, const gs_opts* op
   L.split = take((size_t)L.long_cap * 12 * NT * 4);
   int64_t big = n > n_tiles ? n : n_tiles;
   if (L.rec_cap > big) big = L.rec_cap;
-  // (the per-Gaussian count scans run as one pair: twice a scan's scratch over n)
-  size_t s1 = gs_launch::scan_scratch_ints(big);
-  if (2 * gs_launch::scan_scratch_ints(n) > s1) s1 = 2 * gs_launch::scan_scratch_ints(n);
+  const size_t s1 = gs_launch::scan_scratch_ints(big);
   const size_t s2 = gs_launch::frame_sort_scratch_ints(cap);
   L.scratch_ints = s1 > s2 ? s1 : s2;
   L.scratch = take(L.scratch_ints * 4);
@@ -335,7 +333,7 @@ int gs_project(const gs_params* p, const gs_frame* f, const gs_opts* o, void* st
   if (p->n != f->n) return fail(GS_ERR_ARG, "params n %lld != frame n %lld", (long long)p->n, (long long)f->n);
   if (o->tile_w != f->tile_w || o->tile_h != f->tile_h) return fail(GS_ERR_ARG, "tile size differs from the frame");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  GS_HIP(gs_launch::fill_i32(f->counters, 0, 2, st), "gs_project: clear counters");
+  GS_HIP(gs_launch::clear_project(*f, st), "gs_project: clear counters");
   GS_HIP(gs_launch::project(*p, *f, *o, st), "gs_project");
   return GS_OK;
 }
@@ -355,7 +353,7 @@ int gs_bin_tiles(const gs_frame* f, const gs_opts* o, int32_t sync_count, int64_
     n_sized = c < f->capacity ? c : f->capacity;
     count_dev = nullptr;
   }
-  GS_HIP(gs_launch::emit(*f, n_sized, st), "gs_bin_tiles: emit");
+  GS_HIP(gs_launch::emit(*f, st), "gs_bin_tiles: emit");
   GS_HIP(gs_launch::sort_by_tile(*f, n_sized, count_dev, st), "gs_bin_tiles: sort by tile");
   GS_HIP(gs_launch::ranges(*f, f->keys[f->sort_passes & 1], n_sized, count_dev, st), "gs_bin_tiles: ranges");
   GS_HIP(gs_launch::tile_schedule(*f, st), "gs_bin_tiles: schedule");

@@ -37,24 +37,10 @@ __device__ __forceinline__ int block_scan_256(int x, int* sh_wave, int* total) {
   return base + incl - x;
 }
 
-// Each block scans kScanTile consecutive items (exclusive) and writes its total.  The items scanned are the
-// first dev_count(dc, n): blocks past them only write a zero total.  A launch with gridDim.y = 2 scans a second
-// array of the same length in its second row of blocks (in_b, out_b, sums_b).
-__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t* in, int32_t* out, int64_t n_sized,
-                                                          int32_t* sums, gs_launch::DevCount dc,
-                                                          const int32_t* in_b = nullptr, int32_t* out_b = nullptr,
-                                                          int32_t* sums_b = nullptr) {
-  if (blockIdx.y) {
-    in = in_b;
-    out = out_b;
-    sums = sums_b;
-  }
+// Each block scans kScanTile consecutive items (exclusive) and writes its total.
+__global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t* in, int32_t* out, int64_t n,
+                                                            int32_t* sums) {
   __shared__ int sh_wave[4];
-  const int64_t n = gs_launch::dev_count(dc, n_sized);
-  if ((int64_t)blockIdx.x * kScanTile >= n) {
-    if (threadIdx.x == 0) sums[blockIdx.x] = 0;
-    return;
-  }
   const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
   // a thread's 16 items as four 16-byte loads and stores when they are all in range and the arrays are aligned
   const bool vec = base + kScanItems <= n &&
@@ -102,16 +88,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_tile(const int32_t* in, i
   if (threadIdx.x == 0) sums[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(kScanThreads) void k_scan_add(int32_t* out, int64_t n_sized, const int32_t* sums,
-                                                         gs_launch::DevCount dc, int32_t* out_b = nullptr,
-                                                         const int32_t* sums_b = nullptr) {
-  if (blockIdx.y) {
-    out = out_b;
-    sums = sums_b;
-  }
-  const int64_t n = gs_launch::dev_count(dc, n_sized);
+__global__ __launch_bounds__(kScanThreads) void k_scan_add(int32_t* out, int64_t n, const int32_t* sums) {
   const int64_t base = (int64_t)blockIdx.x * kScanTile;
-  if (base >= n) return;
   const int add = sums[blockIdx.x];
   for (int i = threadIdx.x; i < kScanTile; i += kScanThreads) {
     const int64_t idx = base + i;
@@ -402,89 +380,182 @@ constexpr int kRecCount = 196;
 // when the record list itself overflowed), set by the record list's first thread.
 constexpr int kInstSum = 197;
 
+// Running sums over blocks of 256 items (Gaussians, sorted records) without a scan: the kernel that forms the items'
+// counts leaves each block's total and adds it to the total of its group of kGroup blocks; a block of the consumer sums
+// the groups and then the blocks before it, a wave by itself.  (Scans of the items took three launches, 14 us, each.)
+constexpr int kGroup = gsk::kTotalsGroup;
+
+// part_before only loads, so that a caller can have its own loads in flight beside them before it sums the lanes.
+__device__ __forceinline__ int64_t part_before(const int32_t* __restrict__ blocks,
+                                               const unsigned long long* __restrict__ groups, int64_t b) {
+  const int lane = __lane_id();
+  const int64_t grp = b / kGroup;
+  int64_t x = lane < (int)(b % kGroup) ? blocks[grp * kGroup + lane] : 0;
+  for (int64_t i0 = 0; i0 < grp; i0 += 256) {  // four loads in flight
+    unsigned long long v[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = i0 + 64 * k + lane < grp ? groups[i0 + 64 * k + lane] : 0;
+    x += (int64_t)((v[0] + v[1]) + (v[2] + v[3]));
+  }
+  return x;
+}
+
 __device__ __forceinline__ int rect_area(const short4 rc) { return (rc.y - rc.x + 1) * (rc.w - rc.z + 1); }
 
 // ... and each visible record's first partial slot.  The instances of a wave's 64 Gaussians occupy one run of
 // slots from inst_first[g0] (g0 the wave's first Gaussian), laid out in the record list's order: view by view,
 // Gaussians ascending within a view; so the projection backward, which takes the views together, reads each
 // view's partials of the wave as one contiguous run.  Wide records (more than kWideRecord tiles) are appended
-// to big_rec (count in counters[kBigCount], one atomic per wave; the list order is not fixed, which nothing
-// depends on).
+// to big_rec (count in counters[kBigCount], one atomic per block: they queue at about 5 ns each, 30 us of a view
+// whose every wave held some; the list order is not fixed, which nothing depends on).
 constexpr int kBigCount = 198;
 constexpr int kFrameCounters = 256;  // the frame's counters; behind them the two sorts' zeroed words
 
+//
+// With many views the reads of rectangles and depths, 8 and 4 bytes a visible record in rows of n, set the time:
+// kViewBatch views' reads are in flight together.
+constexpr int kViewBatch = 4;
+constexpr int kWideList = 1024;
+
 __global__ __launch_bounds__(256) void k_record_list(const uint64_t* __restrict__ vis_mask,
                                                     const int32_t* __restrict__ n_rec,
-                                                    const int32_t* __restrict__ first,
-                                                    const int32_t* __restrict__ inst_first,
-                                                    const int32_t* __restrict__ n_inst,
+                                                    const int32_t* __restrict__ n_inst, gsk::Totals tot,
+                                                    int32_t* __restrict__ first, int32_t* __restrict__ inst_first,
                                                     const short4* __restrict__ rect,
                                                     const uint32_t* __restrict__ zbits, int V, int64_t n, int64_t rcap,
                                                     uint32_t* __restrict__ rkeys, int32_t* __restrict__ rvals,
                                                     int32_t* __restrict__ rec_slot, int32_t* __restrict__ big_rec,
                                                     int32_t* __restrict__ counters, int64_t capacity) {
+  __shared__ int s_rec[4], s_inst[4];
+  __shared__ int32_t s_wide[kWideList];
+  __shared__ int s_wides, s_wide_at;
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g == 0) {
-    // the record count R, and counters[0] = the instance total (the end of the per-Gaussian instance scan; the
-    // full count) with the overflow flag if it is above the capacity
-    counters[kRecCount] = first[n - 1] + n_rec[n - 1];
-    const int64_t total = (int64_t)inst_first[n - 1] + n_inst[n - 1];
+  const int wave = threadIdx.x >> 6;
+  if (threadIdx.x == 0) s_wides = 0;
+  const bool here = g < n;
+  const uint64_t m = here ? vis_mask[g] : 0ull;
+  const int my_rec = here ? n_rec[g] : 0, my_inst = here ? n_inst[g] : 0;
+  int64_t c = part_before(tot.rec, tot.rec_group, blockIdx.x);
+  int64_t inst_base = part_before(tot.inst, tot.inst_group, blockIdx.x);
+  int wave_rec, wave_inst;
+  const int rec_ex = gsk::wave_excl_scan(my_rec, wave_rec), inst_ex = gsk::wave_excl_scan(my_inst, wave_inst);
+  if (__lane_id() == 0) {
+    s_rec[wave] = wave_rec;
+    s_inst[wave] = wave_inst;
+  }
+  c = gsk::wave_sum64(c);
+  inst_base = gsk::wave_sum64(inst_base);
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) {
+    c += s_rec[w];
+    inst_base += s_inst[w];
+  }
+  if (here) {
+    first[g] = (int32_t)c + rec_ex;
+    inst_first[g] = (int32_t)inst_base + inst_ex;
+  }
+  if (g == n - 1) {
+    // the record count R, and counters[0] = the instance total (the full count) with the overflow flag if it is above
+    // the capacity
+    const int64_t total = inst_base + inst_ex + my_inst;
+    counters[kRecCount] = (int32_t)c + rec_ex + my_rec;
     counters[kInstSum] = (int32_t)total;
     counters[0] = (int32_t)total;
     if (total > capacity) atomicOr(counters + 1, GS_FLAG_INSTANCE_OVERFLOW);
   }
-  const bool here = g < n;
-  const uint64_t m = here ? vis_mask[g] : 0ull;
-  // The wave's records start where its first Gaussian's do (the scan of the record counts) and are listed view
-  // by view, each view's records in lane (Gaussian) order, so that every read and write of a view is one
-  // coalesced run.  Within a view the list keeps ascending Gaussian index, which is all the depth sort's tie rule
-  // needs (records of different views never share a tile).
-  const int64_t g0 = g - __lane_id();
-  int64_t c = __builtin_amdgcn_readfirstlane((int)(g0 < n ? first[g0] : 0));
-  int32_t slot_c = __builtin_amdgcn_readfirstlane((int)(g0 < n ? inst_first[g0] : 0));
+  // The wave's records start where its first Gaussian's do and are listed view by view, each view's records in lane
+  // (Gaussian) order, so that every read and write of a view is one coalesced run.  Within a view the list keeps
+  // ascending Gaussian index, which is all the depth sort's tie rule needs (records of different views never share a
+  // tile).
+  int32_t slot_c = (int32_t)inst_base;
   const uint64_t lt = gsk::lanemask_lt();
-  for (int v = 0; v < V; ++v) {
-    const bool vis = (m >> v) & 1ull;
-    const uint64_t vb = __ballot(vis);
-    if (vb == 0) continue;
-    const int64_t pos = c + __popcll(vb & lt);
-    c += __popcll(vb);
-    const int64_t r = (int64_t)v * n + g;
-    const int area = vis ? rect_area(rect[r]) : 0;
-    int view_total;
-    const int before = gsk::wave_excl_scan(area, view_total);
-    const int32_t slot = slot_c + before;
-    slot_c += view_total;
-    if (!vis) continue;
-    if (pos < rcap) {
-      rkeys[pos] = zbits[r];
-      rvals[pos] = (int32_t)r;
+  for (int v0 = 0; v0 < V; v0 += kViewBatch) {
+    if (__ballot((m >> v0) != 0) == 0) break;
+    short4 rcs[kViewBatch];
+    uint32_t zs[kViewBatch];
+#pragma unroll
+    for (int i = 0; i < kViewBatch; ++i) {
+      const bool vis = v0 + i < V && (m >> (v0 + i)) & 1ull;
+      const int64_t r = (int64_t)(v0 + i) * n + g;
+      rcs[i] = make_short4(0, -1, 0, -1);
+      zs[i] = 0;
+      if (vis) {
+        rcs[i] = rect[r];
+        zs[i] = zbits[r];
+      }
     }
-    rec_slot[r] = slot;
-    const bool wide = area > gsk::kWideRecord;
-    const uint64_t wb = __ballot(wide);
-    if (wb) {
-      const int lead = __builtin_ctzll(wb);
-      int base = 0;
-      if (__lane_id() == lead) base = atomicAdd(counters + kBigCount, __popcll(wb));
-      base = __builtin_amdgcn_readlane(base, lead);
-      const int bpos = base + __popcll(wb & lt);
-      if (wide && bpos < rcap) big_rec[bpos] = (int32_t)r;
+#pragma unroll
+    for (int i = 0; i < kViewBatch; ++i) {
+      const bool vis = v0 + i < V && (m >> (v0 + i)) & 1ull;
+      const uint64_t vb = __ballot(vis);
+      if (vb == 0) continue;
+      const int64_t pos = c + __popcll(vb & lt);
+      c += __popcll(vb);
+      const int64_t r = (int64_t)(v0 + i) * n + g;
+      const int area = rect_area(rcs[i]);  // (0 for the empty rectangle)
+      int view_total;
+      const int before = gsk::wave_excl_scan(area, view_total);
+      const int32_t slot = slot_c + before;
+      slot_c += view_total;
+      if (!vis) continue;
+      if (pos < rcap) {
+        rkeys[pos] = zs[i];
+        rvals[pos] = (int32_t)r;
+      }
+      rec_slot[r] = slot;
+      const bool wide = area > gsk::kWideRecord;
+      const uint64_t wb = __ballot(wide);
+      if (wb) {
+        const int lead = __builtin_ctzll(wb);
+        int base = 0;
+        if (__lane_id() == lead) base = atomicAdd(&s_wides, __popcll(wb));
+        base = __builtin_amdgcn_readlane(base, lead);
+        const int at = base + __popcll(wb & lt);
+        if (wide && at < kWideList) {
+          s_wide[at] = (int32_t)r;
+        } else if (wide) {  // (more of them than the block's list holds)
+          const int bpos = atomicAdd(counters + kBigCount, 1);
+          if (bpos < rcap) big_rec[bpos] = (int32_t)r;
+        }
+      }
     }
   }
+  __syncthreads();
+  const int wides = min(s_wides, kWideList);
+  if (wides == 0) return;
+  if (threadIdx.x == 0) s_wide_at = atomicAdd(counters + kBigCount, wides);
+  __syncthreads();
+  for (int i = threadIdx.x; i < wides; i += 256)
+    if (s_wide_at + i < rcap) big_rec[s_wide_at + i] = s_wide[i];
 }
 
-// Instance count of each depth-sorted record (its tile rectangle's area), and the rectangle itself in sorted
-// order (tx0 | tx1 << 16 in rx[j], ty0 | ty1 << 16 in ry[j]) so that the emission reads it in coalesced runs.
-__global__ void k_record_counts(const int32_t* __restrict__ rvals, const short4* __restrict__ rect,
-                                const int32_t* __restrict__ counters, int64_t rcap, int32_t* __restrict__ cnt,
-                                uint32_t* __restrict__ rx, uint32_t* __restrict__ ry) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= sort_count(counters + kRecCount, rcap, rcap)) return;
-  const short4 rc = rect[rvals[j]];
-  cnt[j] = rect_area(rc);
-  rx[j] = (uint32_t)(uint16_t)rc.x | ((uint32_t)(uint16_t)rc.y << 16);
-  ry[j] = (uint32_t)(uint16_t)rc.z | ((uint32_t)(uint16_t)rc.w << 16);
+// The tile rectangle of each depth-sorted record, in sorted order (tx0 | tx1 << 16 in rx[j], ty0 | ty1 << 16 in ry[j]) so
+// that the emission reads it in coalesced runs, and the totals of their instance counts.
+__global__ __launch_bounds__(256) void k_record_counts(const int32_t* __restrict__ rvals,
+                                                       const short4* __restrict__ rect,
+                                                       const int32_t* __restrict__ counters, int64_t rcap,
+                                                       uint32_t* __restrict__ rx, uint32_t* __restrict__ ry,
+                                                       int32_t* __restrict__ blocks,
+                                                       unsigned long long* __restrict__ groups,
+                                                       int32_t* __restrict__ waves) {
+  __shared__ int s_cnt[4];
+  const int64_t R = sort_count(counters + kRecCount, rcap, rcap);
+  for (int64_t b = blockIdx.x; b * 256 < R; b += gridDim.x) {
+    const int64_t j = b * 256 + threadIdx.x;
+    int cnt = 0;
+    if (j < R) {
+      const short4 rc = rect[rvals[j]];
+      cnt = rect_area(rc);
+      rx[j] = (uint32_t)(uint16_t)rc.x | ((uint32_t)(uint16_t)rc.y << 16);
+      ry[j] = (uint32_t)(uint16_t)rc.z | ((uint32_t)(uint16_t)rc.w << 16);
+    }
+    gsk::leave_totals<1>({cnt}, s_cnt, {blocks}, {groups}, b);
+    if (threadIdx.x < 4) {  // and where each wave's records start in the block, so that the emission's waves are by themselves
+      int before = 0;
+      for (int w = 0; w < (int)threadIdx.x; ++w) before += s_cnt[w];
+      waves[4 * b + threadIdx.x] = before;
+    }
+  }
 }
 
 // Records with more tiles than this are emitted by a whole wave, a tile per lane.
@@ -496,16 +567,18 @@ __device__ __forceinline__ int64_t read_lane64(int64_t x, int l) {
   return (int64_t)(((uint64_t)hi << 32) | lo);
 }
 
-// One thread per depth-sorted record: its run of instances (tiles row by row) starts at eo[j]; key = global tile
-// id, value = record id.  Records with more than kSolo tiles are written by the whole wave, a tile per lane.  The
-// runs of a wave's records are consecutive (eo is their exclusive scan), so the other records are first laid out
+// One thread per depth-sorted record: its run of instances (tiles row by row) starts at the sum of the counts before it;
+// key = global tile id, value = record id.  Records with more than kSolo tiles are written by the whole wave, a tile per lane.  The
+// runs of a wave's records are consecutive, so the other records are first laid out
 // in a per-wave LDS window of kEmitWin instances and then stored by the wave in coalesced runs, a window at a
 // time; positions of wide records in a window are marked empty and skipped by the copy.
 constexpr int kEmitWin = 512;
 constexpr uint32_t kEmitEmpty = 0xffffffffu;  // no tile id takes this value
 
-__global__ __launch_bounds__(256) void k_emit(const int32_t* __restrict__ rvals, const int32_t* __restrict__ eo,
-                                             const uint32_t* __restrict__ rx, const uint32_t* __restrict__ ry,
+__global__ __launch_bounds__(256) void k_emit(const int32_t* __restrict__ rvals, const int32_t* __restrict__ blocks,
+                                             const unsigned long long* __restrict__ groups,
+                                             const int32_t* __restrict__ waves, const uint32_t* __restrict__ rx,
+                                             const uint32_t* __restrict__ ry,
                                              const gs_camera* __restrict__ cams,
                                              int V, int64_t n, const int32_t* __restrict__ counters, int64_t rcap,
                                              int64_t capacity, uint32_t* __restrict__ keys,
@@ -513,87 +586,121 @@ __global__ __launch_bounds__(256) void k_emit(const int32_t* __restrict__ rvals,
   __shared__ uint32_t wkey[4][kEmitWin];
   __shared__ int32_t wval[4][kEmitWin];
   const int64_t R = sort_count(counters + kRecCount, rcap, rcap);
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const bool here = j < R;
-  int64_t r = 0, o = 0;
-  short4 rc = make_short4(0, -1, 0, -1);
-  int toff = 0, tx_n = 1;
-  if (here) {
-    r = rvals[j];
-    o = eo[j];
-    const uint32_t x = rx[j], y = ry[j];
-    rc = make_short4((short)(x & 0xffffu), (short)(x >> 16), (short)(y & 0xffffu), (short)(y >> 16));
-    const int v = (int)((uint32_t)r / (uint32_t)n);  // r < 2^31
-    toff = cams[v].tile_offset;
-    tx_n = cams[v].tiles_x;
-  }
-  const int w = rc.y - rc.x + 1, cnt = here ? w * (rc.w - rc.z + 1) : 0;
-  const uint64_t present = __ballot(here);
-  if (present == 0) return;  // the same in every lane of the wave
-  uint64_t big = __ballot(cnt > kSolo);
-  // the wave's instances are [lo, hi): the records of lanes 0 .. last are consecutive in the sorted list
-  const int last = 63 - __builtin_clzll(present);
-  const int64_t lo = read_lane64(o, 0), hi = read_lane64(o + cnt, last);
-  uint32_t* wk = wkey[wv];
-  int32_t* wvv = wval[wv];
-  for (int64_t win = lo; win < hi; win += kEmitWin) {
-    if (big) {
-      for (int i = lane; i < kEmitWin; i += 64) wk[i] = kEmitEmpty;
+  for (int64_t blk = blockIdx.x; blk * 256 < R; blk += gridDim.x) {
+    const int64_t j = blk * 256 + threadIdx.x;
+    const bool here = j < R;
+    const int64_t jj = here ? j : R - 1;
+    const int64_t r = rvals[jj];
+    const uint32_t x = rx[jj], y = ry[jj];
+    const int64_t part = part_before(blocks, groups, blk);
+    const int start = waves[4 * blk + wv];
+    short4 rc = make_short4(0, -1, 0, -1);
+    int toff = 0, tx_n = 1;
+    if (here) {
+      rc = make_short4((short)(x & 0xffffu), (short)(x >> 16), (short)(y & 0xffffu), (short)(y >> 16));
+      const int v = (int)((uint32_t)r / (uint32_t)n);  // r < 2^31
+      toff = cams[v].tile_offset;
+      tx_n = cams[v].tiles_x;
     }
-    if (here && cnt <= kSolo) {
-      const int64_t k0 = max(o, win) - o, k1 = min(o + cnt, win + kEmitWin) - o;
-      if (k0 < k1) {
-        int ty = rc.z + (int)k0 / w, tx = rc.x + (int)k0 % w;
-        for (int64_t k = k0; k < k1; ++k) {
-          const int i = (int)(o + k - win);
-          wk[i] = (uint32_t)(toff + ty * tx_n + tx);
-          wvv[i] = (int32_t)r;
-          if (++tx > rc.y) {
-            tx = rc.x;
-            ++ty;
-          }
+    const int w = rc.y - rc.x + 1, cnt = here ? w * (rc.w - rc.z + 1) : 0;
+    int wave_cnt;
+    const int64_t o = gsk::wave_sum64(part) + start + gsk::wave_excl_scan(cnt, wave_cnt);
+    const uint64_t present = __ballot(here);
+    if (present == 0) continue;  // the same in every lane of the wave
+    uint64_t big = __ballot(cnt > kSolo);
+    // the wave's instances are [lo, hi): the records of lanes 0 .. last are consecutive in the sorted list
+    const int last = 63 - __builtin_clzll(present);
+    const int64_t lo = read_lane64(o, 0), hi = read_lane64(o + cnt, last);
+    uint32_t* wk = wkey[wv];
+    int32_t* wvv = wval[wv];
+    const bool direct = hi - lo > 64 * kSolo;  // mostly wide records' runs: more windows to walk than to fill
+    if (direct && here && cnt <= kSolo) {
+      int id = toff + rc.z * tx_n + rc.x, x = 0;
+      for (int64_t q = o; q < min(o + cnt, capacity); ++q) {
+        keys[q] = (uint32_t)id;
+        vals[q] = (int32_t)r;
+        ++id;
+        if (++x == w) {
+          x = 0;
+          id += tx_n - w;
         }
       }
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // the wave's LDS writes land before its reads
-    const int m = (int)min<int64_t>(kEmitWin, hi - win);
-    for (int i = lane; i < m; i += 64) {
-      const uint32_t kk = wk[i];
-      const int64_t q = win + i;
-      if (kk != kEmitEmpty && q < capacity) {
-        keys[q] = kk;
-        vals[q] = wvv[i];
+    for (int64_t win = lo; win < hi && !direct; win += kEmitWin) {
+      if (big) {
+        for (int i = lane; i < kEmitWin; i += 64) wk[i] = kEmitEmpty;
       }
+      if (here && cnt <= kSolo) {
+        const int64_t k0 = max(o, win) - o, k1 = min(o + cnt, win + kEmitWin) - o;
+        if (k0 < k1) {
+          int ty = rc.z + (int)k0 / w, tx = rc.x + (int)k0 % w;
+          for (int64_t k = k0; k < k1; ++k) {
+            const int i = (int)(o + k - win);
+            wk[i] = (uint32_t)(toff + ty * tx_n + tx);
+            wvv[i] = (int32_t)r;
+            if (++tx > rc.y) {
+              tx = rc.x;
+              ++ty;
+            }
+          }
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // the wave's LDS writes land before its reads
+      const int m = (int)min<int64_t>(kEmitWin, hi - win);
+      for (int i = lane; i < m; i += 64) {
+        const uint32_t kk = wk[i];
+        const int64_t q = win + i;
+        if (kk != kEmitEmpty && q < capacity) {
+          keys[q] = kk;
+          vals[q] = wvv[i];
+        }
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // and its reads before the next window's writes
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");  // and its reads before the next window's writes
-  }
-  while (big) {
-    const int L = __builtin_ctzll(big);
-    big &= big - 1;
-    const int64_t oL = read_lane64(o, L), rL = read_lane64(r, L);
-    const int cL = __builtin_amdgcn_readlane(cnt, L), wL = __builtin_amdgcn_readlane(w, L);
-    const int x0 = __builtin_amdgcn_readlane((int)rc.x, L), y0 = __builtin_amdgcn_readlane((int)rc.z, L);
-    const int toL = __builtin_amdgcn_readlane(toff, L), txL = __builtin_amdgcn_readlane(tx_n, L);
-    for (int k = lane; k < cL; k += 64) {
-      const int64_t q = oL + k;
-      if (q < capacity) {
-        const int ty = y0 + k / wL, tx = x0 + k % wL;
-        keys[q] = (uint32_t)(toL + ty * txL + tx);
-        vals[q] = (int32_t)rL;
+    // wide records, a tile per lane: lane k's first tile, then 64 tiles on, which is dq rows and dr tiles (no division in
+    // the loop: the nearest records are the widest and meet in a few waves, whose time is the kernel's)
+    const int dq = 64 / max(w, 1), dr = 64 - dq * w;
+    const float inv_w = 1.f / (float)max(w, 1);
+    while (big) {
+      const int L = __builtin_ctzll(big);
+      big &= big - 1;
+      const int64_t oL = read_lane64(o, L);
+      const int rL = __builtin_amdgcn_readlane((int)r, L);
+      const int cL = __builtin_amdgcn_readlane(cnt, L), wL = __builtin_amdgcn_readlane(w, L);
+      const int x0 = __builtin_amdgcn_readlane((int)rc.x, L), y0 = __builtin_amdgcn_readlane((int)rc.z, L);
+      const int toL = __builtin_amdgcn_readlane(toff, L), txL = __builtin_amdgcn_readlane(tx_n, L);
+      const int dqL = __builtin_amdgcn_readlane(dq, L), drL = __builtin_amdgcn_readlane(dr, L);
+      const float invL = gsk::read_lane(inv_w, L);
+      const int row = (int)(((float)lane + 0.5f) * invL);  // lane / wL (half a tile from every whole row)
+      int x = lane - row * wL;
+      int id = toL + (y0 + row) * txL + x0 + x;
+      const int m = (int)max<int64_t>(0, min<int64_t>(cL, capacity - oL));
+      uint32_t* kq = keys + oL;
+      int32_t* vq = vals + oL;
+      const int step = dqL * txL + drL, wrap = txL - wL;
+      for (int k = lane; k < m; k += 64) {
+        kq[k] = (uint32_t)id;
+        vq[k] = rL;
+        x += drL;
+        id += step;
+        if (x >= wL) {
+          x -= wL;
+          id += wrap;
+        }
       }
     }
   }
 }
 
-__global__ void k_ranges(const uint32_t* __restrict__ keys, const int32_t* __restrict__ count_dev, int64_t n_sized,
-                         int64_t cap, int2* __restrict__ range) {
+__global__ __launch_bounds__(256) void k_ranges(const uint32_t* __restrict__ keys, const int32_t* __restrict__ count_dev,
+                                                int64_t n_sized, int64_t cap, int2* __restrict__ range) {
   const int64_t n = sort_count(count_dev, n_sized, cap);
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const uint32_t t = keys[i];
-  if (i == 0 || keys[i - 1] != t) range[t].x = (int)i;
-  if (i == n - 1 || keys[i + 1] != t) range[t].y = (int)(i + 1);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+    const uint32_t t = keys[i];
+    if (i == 0 || keys[i - 1] != t) range[t].x = (int)i;
+    if (i == n - 1 || keys[i + 1] != t) range[t].y = (int)(i + 1);
+  }
 }
 
 // Compositing schedule: tiles in descending order of their list length, bucketed by floor(log2(len + 1))
@@ -782,6 +889,9 @@ __global__ __launch_bounds__(1024) void k_schedule_small(const int2* __restrict_
 }
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// Blocks of 256 threads over items whose number only the device knows, which may be far below the capacity: every block
+// costs about 0.3 ns to start and end (25 us for a capacity of 24 M), so they stride over the items from here on.
+inline unsigned strided_blocks(int64_t cap) { return (unsigned)std::min<int64_t>(cdiv(cap, 256), 4096); }
 inline int64_t align64(int64_t a) { return (a + 63) & ~int64_t(63); }
 
 }  // namespace
@@ -797,37 +907,20 @@ size_t scan_scratch_ints(int64_t n) {
   return total + 64;
 }
 
-hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t st, DevCount dc) {
+hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t st) {
   if (n <= 0) return hipSuccess;
   const int64_t nb = cdiv(n, kScanTile);
   int32_t* sums = scratch;
-  k_scan_tile<<<(unsigned)nb, kScanThreads, 0, st>>>(in, out, n, sums, dc);
+  k_scan_tile<<<(unsigned)nb, kScanThreads, 0, st>>>(in, out, n, sums);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (nb > 1) {
-    e = scan_exclusive(sums, sums, nb, scratch + align64(nb), st, DevCount{});
+    e = scan_exclusive(sums, sums, nb, scratch + align64(nb), st);
     if (e != hipSuccess) return e;
-    k_scan_add<<<(unsigned)nb, kScanThreads, 0, st>>>(out, n, sums, dc);
+    k_scan_add<<<(unsigned)nb, kScanThreads, 0, st>>>(out, n, sums);
     return hipGetLastError();
   }
   return hipSuccess;
-}
-
-// Two exclusive scans of arrays of the same length in the launches of one (each kernel covers both).  Scratch:
-// 2 * scan_scratch_ints(n).
-static hipError_t scan_exclusive_pair(const int32_t* in0, int32_t* out0, const int32_t* in1, int32_t* out1,
-                                      int64_t n, int32_t* scratch, hipStream_t st) {
-  if (n <= 0) return hipSuccess;
-  const int64_t nb = cdiv(n, kScanTile);
-  int32_t* sums0 = scratch;
-  int32_t* sums1 = scratch + align64(nb);
-  k_scan_tile<<<dim3((unsigned)nb, 2), kScanThreads, 0, st>>>(in0, out0, n, sums0, DevCount{}, in1, out1, sums1);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || nb == 1) return e;
-  if ((e = scan_exclusive_pair(sums0, sums0, sums1, sums1, nb, scratch + 2 * align64(nb), st)) != hipSuccess)
-    return e;
-  k_scan_add<<<dim3((unsigned)nb, 2), kScanThreads, 0, st>>>(out0, n, sums0, DevCount{}, out1, sums1);
-  return hipGetLastError();
 }
 
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t st) {
@@ -890,39 +983,74 @@ hipError_t sort_by_tile(const gs_frame& f, int64_t n_sized, const int32_t* count
                              f.counters + kFrameCounters + kSortZero32, f.scratch, st);
 }
 
-size_t counter_ints() { return kFrameCounters + 2 * (size_t)kSortZero32; }
+// Behind the frame's counters: the words of its two sorts, the emission's group totals (both cleared by binning), the
+// projection's group totals (cleared by it), and the block totals.
+constexpr int kGroupItems = 256 * kGroup;
+
+struct EmitTotals {
+  int32_t *blocks, *waves;
+  unsigned long long* groups;
+};
+gsk::Totals project_totals(const gs_frame& f);
+static EmitTotals emit_totals(const gs_frame& f) {
+  EmitTotals t;
+  t.groups = reinterpret_cast<unsigned long long*>(f.counters + kFrameCounters + 2 * kSortZero32);
+  const gsk::Totals p = project_totals(f);
+  t.blocks = p.inst + align64(cdiv(f.n, 256));
+  t.waves = t.blocks + align64(cdiv(f.rec_cap, 256));
+  return t;
+}
+gsk::Totals project_totals(const gs_frame& f) {
+  gsk::Totals t;
+  const int64_t groups = cdiv(f.n, kGroupItems);
+  t.rec_group = reinterpret_cast<unsigned long long*>(f.counters + kFrameCounters + 2 * kSortZero32) +
+                cdiv(f.rec_cap, kGroupItems);
+  t.inst_group = t.rec_group + groups;
+  t.rec = reinterpret_cast<int32_t*>(t.inst_group + groups);
+  t.inst = t.rec + align64(cdiv(f.n, 256));
+  return t;
+}
+
+size_t counter_ints(int64_t n, int64_t rec_cap) {
+  return (size_t)(kFrameCounters + 2 * kSortZero32 + 2 * (cdiv(rec_cap, kGroupItems) + 2 * cdiv(n, kGroupItems)) +
+                  2 * align64(cdiv(n, 256)) + 5 * align64(cdiv(rec_cap, 256)));
+}
+
+hipError_t clear_project(const gs_frame& f, hipStream_t st) {
+  const int64_t m = 4 * cdiv(f.n, kGroupItems);
+  k_fill2_i32<<<(unsigned)cdiv(m, 256), 256, 0, st>>>(f.counters, 2,
+                                                      reinterpret_cast<int32_t*>(project_totals(f).rec_group), m, 0);
+  return hipGetLastError();
+}
 
 // Binning up to the instance total: the records' first partial slots, the record list sorted by depth (record ids
-// in rvals[0]), each sorted record's tile rectangle (rkeys[0], rkeys[1]) and first emission index (rvals[1]), the
+// in rvals[0]), each sorted record's tile rectangle (rkeys[0], rkeys[1]) and the totals of their instance counts, the
 // instance total and the overflow flag.
 hipError_t bin_records(const gs_frame& f, hipStream_t st) {
   const int64_t rcap = f.rec_cap;
-  // kInstSum, kBigCount (and the unused counters) and the two sorts' words behind the counters
-  hipError_t e = fill_i32(f.counters + kInstSum, 0, (int64_t)counter_ints() - kInstSum, st);
+  // kInstSum, kBigCount (and the unused counters), the two sorts' words and the emission's group totals
+  hipError_t e = fill_i32(f.counters + kInstSum, 0,
+                          kFrameCounters - kInstSum + 2 * kSortZero32 + 2 * cdiv(rcap, kGroupItems), st);
   if (e != hipSuccess) return e;
-  if ((e = scan_exclusive_pair(f.n_rec, f.rec_first, f.n_inst, f.inst_first, f.n, f.scratch, st)) != hipSuccess)
-    return e;
-  k_record_list<<<(unsigned)cdiv(f.n, 256), 256, 0, st>>>(f.vis_mask, f.n_rec, f.rec_first, f.inst_first, f.n_inst,
-                                                          reinterpret_cast<const short4*>(f.rect), f.zbits, f.n_views,
-                                                          f.n, rcap, f.rkeys[0], f.rvals[0], f.rec_slot, f.big_rec,
-                                                          f.counters, f.capacity);
+  k_record_list<<<(unsigned)cdiv(f.n, 256), 256, 0, st>>>(f.vis_mask, f.n_rec, f.n_inst, project_totals(f), f.rec_first,
+                                                          f.inst_first, reinterpret_cast<const short4*>(f.rect), f.zbits,
+                                                          f.n_views, f.n, rcap, f.rkeys[0], f.rvals[0], f.rec_slot,
+                                                          f.big_rec, f.counters, f.capacity);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = sort_impl<uint32_t>(f.rkeys[0], f.rvals[0], f.rkeys[1], f.rvals[1], rcap, f.counters + kRecCount, rcap, 32,
                                f.counters + kFrameCounters, f.scratch, st)) != hipSuccess)
     return e;  // 4 passes: the sorted records are back in rkeys[0] / rvals[0]
-  // counts straight into rvals[1], scanned in place into the emission offsets; the sorted rectangles take the
-  // depth keys' buffers, which are no longer needed
-  k_record_counts<<<(unsigned)cdiv(rcap, 256), 256, 0, st>>>(f.rvals[0], reinterpret_cast<const short4*>(f.rect),
-                                                             f.counters, rcap, f.rvals[1], f.rkeys[0], f.rkeys[1]);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = scan_exclusive(f.rvals[1], f.rvals[1], rcap, f.scratch, st,
-                          DevCount{f.counters + kRecCount, rcap, 1, 1})) != hipSuccess)
-    return e;
-  return hipSuccess;
+  // the sorted rectangles take the depth keys' buffers, which are no longer needed
+  const EmitTotals t = emit_totals(f);
+  k_record_counts<<<strided_blocks(rcap), 256, 0, st>>>(f.rvals[0], reinterpret_cast<const short4*>(f.rect),
+                                                             f.counters, rcap, f.rkeys[0], f.rkeys[1], t.blocks,
+                                                             t.groups, t.waves);
+  return hipGetLastError();
 }
 
-hipError_t emit(const gs_frame& f, int64_t /*n_sized*/, hipStream_t st) {
-  k_emit<<<(unsigned)cdiv(f.rec_cap, 256), 256, 0, st>>>(f.rvals[0], f.rvals[1], f.rkeys[0], f.rkeys[1], f.cams,
+hipError_t emit(const gs_frame& f, hipStream_t st) {
+  const EmitTotals t = emit_totals(f);
+  k_emit<<<strided_blocks(f.rec_cap), 256, 0, st>>>(f.rvals[0], t.blocks, t.groups, t.waves, f.rkeys[0], f.rkeys[1], f.cams,
                                                          f.n_views, f.n, f.counters, f.rec_cap, f.capacity, f.keys[0],
                                                          f.vals[0]);
   return hipGetLastError();
@@ -969,7 +1097,7 @@ hipError_t ranges(const gs_frame& f, const uint32_t* keys, int64_t n_sized, cons
   k_fill2_i32<<<(unsigned)cdiv(nr > 32 ? nr : 32, 256), 256, 0, st>>>(f.tile_range, nr, f.counters + 128, 32, 0);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || n_sized <= 0) return e;
-  k_ranges<<<(unsigned)cdiv(n_sized, 256), 256, 0, st>>>(keys, count_dev, n_sized, f.capacity,
+  k_ranges<<<strided_blocks(n_sized), 256, 0, st>>>(keys, count_dev, n_sized, f.capacity,
                                                          reinterpret_cast<int2*>(f.tile_range));
   return hipGetLastError();
 }

@@ -101,15 +101,74 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
 }
 
 // Exclusive prefix sum over the 64 lanes (lane order) of a non-negative int; total = the wave's sum.
+// The value of the lane n before in its row of 16 (0 from outside the row), or of lane 15 of the row before (rows 1 and
+// 3), or of lane 31 (rows 2 and 3): the steps of a scan over the wave.  (In registers; a __shfl_up costs an LDS trip.)
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ int dpp_or_zero(int x) {
+  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, ROWS == 0xf);
+}
+// Called with every lane of the wave active.
 __device__ __forceinline__ int wave_excl_scan(int x, int& total) {
   int incl = x;
-#pragma unroll
-  for (int d = 1; d < 64; d <<= 1) {
-    const int y = __shfl_up(incl, d);
-    if (__lane_id() >= d) incl += y;
-  }
+  incl += dpp_or_zero<0x111>(incl);
+  incl += dpp_or_zero<0x112>(incl);
+  incl += dpp_or_zero<0x114>(incl);
+  incl += dpp_or_zero<0x118>(incl);
+  incl += dpp_or_zero<0x142, 0xa>(incl);
+  incl += dpp_or_zero<0x143, 0xc>(incl);
   total = __builtin_amdgcn_readlane(incl, 63);
   return incl - x;
+}
+
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ int64_t dpp_or_zero64(int64_t x) {
+  const uint32_t lo = (uint32_t)dpp_or_zero<CTRL, ROWS>((int)(uint32_t)x);
+  const uint32_t hi = (uint32_t)dpp_or_zero<CTRL, ROWS>((int)(uint32_t)((uint64_t)x >> 32));
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ int64_t wave_sum64(int64_t x) {
+  x += dpp_or_zero64<0x111>(x);
+  x += dpp_or_zero64<0x112>(x);
+  x += dpp_or_zero64<0x114>(x);
+  x += dpp_or_zero64<0x118>(x);
+  x += dpp_or_zero64<0x142, 0xa>(x);
+  x += dpp_or_zero64<0x143, 0xc>(x);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, 63);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)x >> 32), 63);
+  return (int64_t)(((uint64_t)hi << 32) | lo);
+}
+
+// Totals of a count per Gaussian over the blocks of 256 threads that form them, and over groups of kTotalsGroup blocks.
+constexpr int kTotalsGroup = 64;
+struct Totals {
+  int32_t *rec, *inst;                            // visible records and instances of a block
+  unsigned long long *rec_group, *inst_group;     // ... of a group, added up (cleared before)
+};
+// Called by every thread of a block of 256 with N counts of the 256 items `block`; shared: 4 N ints.
+template <class T, int N>
+struct Few {
+  T v[N];
+};
+template <int N>
+__device__ __forceinline__ void leave_totals(Few<int, N> x, int* shared, Few<int32_t*, N> blocks,
+                                             Few<unsigned long long*, N> groups, int64_t block) {
+  __syncthreads();  // (a block that comes here again has read its last totals)
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    int total;
+    wave_excl_scan(x.v[i], total);
+    if (__lane_id() == 0) shared[4 * i + (threadIdx.x >> 6)] = total;
+  }
+  __syncthreads();
+  if ((int)threadIdx.x < N) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      if ((int)threadIdx.x != i) continue;
+      const int all = shared[4 * i] + shared[4 * i + 1] + shared[4 * i + 2] + shared[4 * i + 3];
+      blocks.v[i][block] = all;
+      if (all) atomicAdd(groups.v[i] + block / kTotalsGroup, (unsigned long long)all);
+    }
+  }
 }
 
 __device__ __forceinline__ float read_lane(float x, int l) {
@@ -154,33 +213,21 @@ hipError_t project(const gs_params& p, const gs_frame& f, const gs_opts& o, hipS
 hipError_t project_bwd(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params& g,
                        hipStream_t s);
 size_t scan_scratch_ints(int64_t n);
-// An element count read on the device: min(n_sized, mul * ceil(min(max(*p, 0), cap) / div)); p == NULL: n_sized.
-struct DevCount {
-  const int32_t* p = nullptr;
-  int64_t cap = 0;
-  int div = 1, mul = 1;
-};
-__device__ __forceinline__ int64_t dev_count(const DevCount& c, int64_t n_sized) {
-  if (!c.p) return n_sized;
-  int64_t k = c.p[0];
-  k = k < 0 ? 0 : (k > c.cap ? c.cap : k);
-  k = (k + c.div - 1) / c.div * c.mul;
-  return k < n_sized ? k : n_sized;
-}
-// Exclusive scan of in[0, n) into out (in place allowed); with a device count only its first dev_count items.
-hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t s,
-                          DevCount dc = DevCount{});
+// Exclusive scan of in[0, n) into out (in place allowed).
+hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t s);
 hipError_t fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t fill_f32(float* p, float v, int64_t n, hipStream_t s);
 // Binning up to the instance total: the records' first partial slots, visible records sorted by depth, their
-// instance counts and first emission indices, counters[0] = instances (overflow flagged).
+// rectangles and the totals of their instance counts, counters[0] = instances (overflow flagged).
 hipError_t bin_records(const gs_frame& f, hipStream_t s);
-hipError_t emit(const gs_frame& f, int64_t n_sized, hipStream_t s);
+hipError_t emit(const gs_frame& f, hipStream_t s);
 size_t sort_scratch_ints(int64_t n);
 // the instances by tile; bin_records has cleared this sort's words behind the counters
 hipError_t sort_by_tile(const gs_frame& f, int64_t n_sized, const int32_t* count_dev, hipStream_t s);
 size_t frame_sort_scratch_ints(int64_t n);  // of a frame's sorts, whose zeroed words lie behind the counters
-size_t counter_ints();  // the frame's counters and the words of its two sorts
+size_t counter_ints(int64_t n, int64_t rec_cap);  // the frame's counters and the words behind them
+gsk::Totals project_totals(const gs_frame& f);
+hipError_t clear_project(const gs_frame& f, hipStream_t s);  // counters[0..1] and the totals that the projection adds to
 hipError_t sort_pairs(uint64_t* k0, int32_t* v0, uint64_t* k1, int32_t* v1, int64_t n_sized,
                       const int32_t* count_dev, int64_t cap, int key_bits, int32_t* scratch, hipStream_t s);
 hipError_t ranges(const gs_frame& f, const uint32_t* keys, int64_t n_sized, const int32_t* count_dev, hipStream_t s);

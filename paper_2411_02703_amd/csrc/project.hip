@@ -187,10 +187,13 @@ __global__ __launch_bounds__(256) void k_project(const float* __restrict__ means
                                                  float4* __restrict__ rec, short4* __restrict__ rect,
                                                  uint64_t* __restrict__ vis_mask,
                                                  uint32_t* __restrict__ zbits, int32_t* __restrict__ n_rec,
-                                                 int32_t* __restrict__ n_inst, int32_t* __restrict__ flags) {
+                                                 int32_t* __restrict__ n_inst, gsk::Totals tot,
+                                                 int32_t* __restrict__ flags) {
   constexpr int K = (DEG + 1) * (DEG + 1);
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= n) return;
+  __shared__ int s_tot[8];
+  const int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const bool here = gi < n;
+  const int64_t g = here ? gi : n - 1;  // (threads past the end read the last Gaussian and do nothing with it)
   float mu[3], ls[3], qq[4], f[K * 3];
   bool finite = true;
   for (int i = 0; i < 3; ++i) {
@@ -212,8 +215,8 @@ __global__ __launch_bounds__(256) void k_project(const float* __restrict__ means
   uint64_t mask = 0;
   int cnt = 0, inst = 0;
   if (!finite) {
-    atomicOr(flags, GS_FLAG_NONFINITE);
-  } else {
+    if (here) atomicOr(flags, GS_FLAG_NONFINITE);
+  } else if (here) {
     Shape s;
     shape_of(ls, qq, ol, s);
     if (s.qnorm > 0.f && s.o >= op.alpha_min) {
@@ -267,9 +270,12 @@ __global__ __launch_bounds__(256) void k_project(const float* __restrict__ means
       }
     }
   }
-  vis_mask[g] = mask;
-  n_rec[g] = cnt;
-  n_inst[g] = inst;
+  if (here) {
+    vis_mask[g] = mask;
+    n_rec[g] = cnt;
+    n_inst[g] = inst;
+  }
+  gsk::leave_totals<2>({cnt, inst}, s_tot, {tot.rec, tot.inst}, {tot.rec_group, tot.inst_group}, blockIdx.x);
 }
 
 // The partials of each wide record (more than kWideRecord tile instances), summed by a wave per record into the
@@ -652,22 +658,27 @@ hipError_t project(const gs_params& p, const gs_frame& f, const gs_opts& o, hipS
   auto* rec = reinterpret_cast<float4*>(f.rec);
   auto* rect = reinterpret_cast<short4*>(f.rect);
   int32_t* flags = f.counters + 1;
+  const gsk::Totals tot = project_totals(f);
   switch (p.sh_degree) {
     case 0:
       k_project<0><<<blocks, threads, 0, st>>>(p.means, p.log_scales, p.quats, p.opacity, p.sh, p.n, f.cams,
-                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, flags);
+                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, tot,
+                                               flags);
       break;
     case 1:
       k_project<1><<<blocks, threads, 0, st>>>(p.means, p.log_scales, p.quats, p.opacity, p.sh, p.n, f.cams,
-                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, flags);
+                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, tot,
+                                               flags);
       break;
     case 2:
       k_project<2><<<blocks, threads, 0, st>>>(p.means, p.log_scales, p.quats, p.opacity, p.sh, p.n, f.cams,
-                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, flags);
+                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, tot,
+                                               flags);
       break;
     default:
       k_project<3><<<blocks, threads, 0, st>>>(p.means, p.log_scales, p.quats, p.opacity, p.sh, p.n, f.cams,
-                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, flags);
+                                               f.n_views, op, rec, rect, f.vis_mask, f.zbits, f.n_rec, f.n_inst, tot,
+                                               flags);
       break;
   }
   return hipGetLastError();
