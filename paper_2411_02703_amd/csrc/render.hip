@@ -1580,7 +1580,10 @@ hipError_t loss_total(const gs_frame& f, hipStream_t st) {
 hipError_t count_valid(const gs_frame& f, const float* tgt_depth, int64_t max_pixels, hipStream_t st) {
   hipError_t e = fill_i32(f.counters + 2, 0, f.n_views, st);
   if (e != hipSuccess) return e;
+  // eight loads a thread, or up to 32 where the views together make more than 512 blocks anyway
   int64_t bx = (max_pixels + 256 * 32 - 1) / (256 * 32);
+  const int64_t wide = (max_pixels + 256 * 8 - 1) / (256 * 8), most = 512 / f.n_views;
+  if (bx < most) bx = wide < most ? wide : most;
   if (bx < 1) bx = 1;
   dim3 grid((unsigned)bx, (unsigned)f.n_views);
   k_count_valid<<<grid, 256, 0, st>>>(tgt_depth, f.cams, f.counters + 2);

@@ -57,3 +57,27 @@ def test_forward_kernel_of_whole_tiles_by_frame_and_list_size(gpu_lib, n, size):
         out = run_gpu(sc, tile=(8, 8), targets=True, fused=True, seg=seg)
         np.testing.assert_allclose(out["loss"], L, rtol=1e-5)
         check_grads(out["grads"], ref, exc, f"n={n} {size} seg={seg}", scale=scale)
+
+
+@pytest.mark.parametrize("sizes", [[(336, 272)], [(341, 275), (16, 17)], [(400, 300), (5, 400), (200, 150)]])
+def test_ssim_over_more_tiles_than_blocks(gpu_lib, sizes):
+    """1071 tiles and channels and more over at most 1024 blocks, aligned and ragged; bounds as for few tiles (a moment
+    is a sum of 121 terms in FP32 either way)."""
+    import torch
+
+    from paper_2411_02703_amd import binding as B
+
+    cams = [scenes.identity_camera(0.8 * w, 0.8 * w, w / 2, h / 2, w, h) for w, h in sizes]
+    for i, c in enumerate(cams):
+        c.weight = 1.0 / (i + 1)
+    total = sum(w * h for w, h in sizes)
+    rng = np.random.default_rng(total)
+    x, y = (rng.uniform(size=3 * total).astype(np.float32) for _ in range(2))
+    fr = B.Frame(10, cams)
+    g, loss = torch.empty(3 * total, device="cuda"), torch.zeros(64, device="cuda")
+    print("ssim", sizes, flush=True)
+    B.gs_ssim(fr, torch.as_tensor(x).cuda(), torch.as_tensor(y).cuda(), 0.2, g, loss)
+    want, gref = oracle.ssim_loss(x, y, cams, 0.2)
+    np.testing.assert_allclose(float(loss[0].item()), want, rtol=1e-5)
+    rms = np.sqrt((gref ** 2).mean())
+    assert np.all(np.abs(g.cpu().numpy().astype(np.float64) - gref) <= 1e-4 * (np.abs(gref) + rms))
