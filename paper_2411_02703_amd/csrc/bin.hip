@@ -218,6 +218,32 @@ struct SortStage {
   int tile;
 };
 
+// The wave's keys (ITEMS rounds of 64 from i0, valid below nvalid) ranked among its keys of the same digit, by ballots;
+// cnt (zero before) ends as the wave's count of each digit.
+template <int ITEMS, class KeyT>
+__device__ __forceinline__ void rank_digit(const KeyT* key, int i0, int nvalid, int shift, uint16_t* cnt, int* pos) {
+  const uint64_t lt = gsk::lanemask_lt();
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const bool valid = i0 + k * 64 < nvalid;
+    const int d = (int)((key[k] >> shift) & 255u);
+    uint64_t peers = __ballot(valid);
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+      const bool bit = (d >> b) & 1;
+      const uint64_t bb = __ballot(bit);
+      peers &= bit ? bb : ~bb;
+    }
+    const int rank = __popcll(peers & lt);
+    int before = 0;
+    if (valid) before = cnt[d];
+    pos[k] = before + rank;
+    __builtin_amdgcn_wave_barrier();
+    if (valid && rank == 0) cnt[d] = (uint16_t)(before + __popcll(peers));
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 template <class KeyT, int ITEMS>
 __device__ __forceinline__ void scatter_tile(SortStage<KeyT>& s, const KeyT* __restrict__ kin,
                                              const int32_t* __restrict__ vin, KeyT* __restrict__ kout,
@@ -238,31 +264,12 @@ __device__ __forceinline__ void scatter_tile(SortStage<KeyT>& s, const KeyT* __r
   const int i0 = wave * 64 * ITEMS + lane;
   KeyT key[ITEMS];
   int pos[ITEMS];
-  const uint64_t lt = gsk::lanemask_lt();
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
     const bool valid = i0 + k * 64 < nvalid;
     key[k] = valid ? kin[i0 + k * 64] : KeyT(0);
   }
-#pragma unroll
-  for (int k = 0; k < ITEMS; ++k) {
-    const bool valid = i0 + k * 64 < nvalid;
-    const int d = (int)((key[k] >> shift) & 255u);
-    uint64_t peers = __ballot(valid);
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const bool bit = (d >> b) & 1;
-      const uint64_t bb = __ballot(bit);
-      peers &= bit ? bb : ~bb;
-    }
-    const int rank = __popcll(peers & lt);
-    int before = 0;
-    if (valid) before = wcnt[wave][d];
-    pos[k] = before + rank;
-    __builtin_amdgcn_wave_barrier();
-    if (valid && rank == 0) wcnt[wave][d] = (uint16_t)(before + __popcll(peers));
-    __builtin_amdgcn_wave_barrier();
-  }
+  rank_digit<ITEMS>(key, i0, nvalid, shift, wcnt[wave], pos);
   __syncthreads();
   // digit tid: the tile's count is published, the waves' first places in the tile and the digit's first place overall
   uint32_t* my_state = state + (int64_t)tile * 256 + tid;
@@ -368,6 +375,98 @@ __global__ __launch_bounds__(kSortThreads, sizeof(KeyT) == 4 ? 8 : 4) void k_sor
     scatter_tile<KeyT, kSmallItems>(s, kin, vin, kout, vout, n, pass, dc, state, next);
   else
     scatter_tile<KeyT, kLargeItems>(s, kin, vin, kout, vout, n, pass, dc, state, next);
+}
+
+// A sort of at most kBlockSort keys: every pass in one block, through its LDS, where the launches of a kernel per pass were
+// the cost.  Four passes over 300 keys take 17 us here and 31 in launches of their own, over 2000 21 and 35, over 6000 39
+// and 41, over 8192 41 and 41 (and a capacity is seldom full).
+constexpr int kBlockSort = kSortThreads * kLargeItems;
+
+template <class KeyT>
+struct BlockStage {
+  KeyT key[kBlockSort];
+  int32_t val[kBlockSort];
+  uint16_t cnt[kSortThreads / 64][256];
+  int wave[4];
+};
+
+template <class KeyT, int ITEMS>
+__device__ __forceinline__ void sort_block(BlockStage<KeyT>& s, const KeyT* __restrict__ kin,
+                                           const int32_t* __restrict__ vin, KeyT* __restrict__ kout,
+                                           int32_t* __restrict__ vout, int n, int passes) {
+  constexpr int WAVES = kSortThreads / 64;
+  const int tid = threadIdx.x, wave = tid >> 6, i0 = wave * 64 * ITEMS + __lane_id();
+  KeyT key[ITEMS];
+  int32_t val[ITEMS];
+  int pos[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const bool valid = i0 + k * 64 < n;
+    key[k] = valid ? kin[i0 + k * 64] : KeyT(0);
+    val[k] = valid ? vin[i0 + k * 64] : 0;
+  }
+  for (int p = 0; p < passes; ++p) {
+    const int shift = 8 * p;
+    for (int i = tid; i < WAVES * 256; i += kSortThreads) (&s.cnt[0][0])[i] = 0;
+    __syncthreads();
+    rank_digit<ITEMS>(key, i0, n, shift, s.cnt[wave], pos);
+    __syncthreads();
+    int first = 0;
+    if (tid < 256) {
+      int total = 0, t;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) total += s.cnt[w][tid];
+      first = gsk::wave_excl_scan(total, t);
+      if (__lane_id() == 0) s.wave[wave] = t;
+    }
+    __syncthreads();
+    if (tid < 256) {
+      for (int w = 0; w < wave; ++w) first += s.wave[w];
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) {
+        const int c = s.cnt[w][tid];
+        s.cnt[w][tid] = (uint16_t)first;
+        first += c;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      if (i0 + k * 64 < n) {
+        const int q = s.cnt[wave][(int)((key[k] >> shift) & 255u)] + pos[k];
+        s.key[q] = key[k];
+        s.val[q] = val[k];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      if (i0 + k * 64 < n) {
+        key[k] = s.key[i0 + k * 64];
+        val[k] = s.val[i0 + k * 64];
+      }
+    }
+  }
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    if (i0 + k * 64 < n) {
+      kout[i0 + k * 64] = key[k];
+      vout[i0 + k * 64] = val[k];
+    }
+  }
+}
+
+template <class KeyT>
+__global__ __launch_bounds__(kSortThreads) void k_sort_block(const KeyT* __restrict__ kin,
+                                                             const int32_t* __restrict__ vin, KeyT* kout, int32_t* vout,
+                                                             const int32_t* __restrict__ count_dev, int64_t n_sized,
+                                                             int64_t cap, int passes) {
+  __shared__ BlockStage<KeyT> s;
+  const int n = (int)sort_count(count_dev, n_sized, cap);
+  if (n <= kSortThreads) sort_block<KeyT, 1>(s, kin, vin, kout, vout, n, passes);
+  else if (n <= 2 * kSortThreads) sort_block<KeyT, 2>(s, kin, vin, kout, vout, n, passes);
+  else if (n <= 4 * kSortThreads) sort_block<KeyT, 4>(s, kin, vin, kout, vout, n, passes);
+  else sort_block<KeyT, 8>(s, kin, vin, kout, vout, n, passes);
 }
 
 // ------------------------------------------------------------------ the record list and the emission
@@ -952,8 +1051,13 @@ template <class KeyT>
 static hipError_t sort_impl(KeyT* k0, int32_t* v0, KeyT* k1, int32_t* v1, int64_t n_sized, const int32_t* count_dev,
                             int64_t cap, int key_bits, int32_t* zeroed, int32_t* states, hipStream_t st) {
   if (n_sized <= 0) return hipSuccess;
-  const int64_t nb = sort_blocks(n_sized);
   const int passes = (key_bits + 7) / 8;
+  if (n_sized <= kBlockSort) {
+    k_sort_block<KeyT><<<1, kSortThreads, 0, st>>>(k0, v0, passes & 1 ? k1 : k0, passes & 1 ? v1 : v0, count_dev, n_sized,
+                                                   cap, passes);
+    return hipGetLastError();
+  }
+  const int64_t nb = sort_blocks(n_sized);
   uint32_t* state[2] = {reinterpret_cast<uint32_t*>(states), reinterpret_cast<uint32_t*>(states) + 256 * nb};
   const int64_t db = cdiv(n_sized, kDigitThreads * kDigitItems);
   k_sort_digits<KeyT><<<(unsigned)(db < kDigitBlocks ? db : kDigitBlocks), kDigitThreads, 0, st>>>(

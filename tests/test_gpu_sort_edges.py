@@ -1,5 +1,5 @@
-"""The radix sort around its tile sizes, its change of tile size (2^19 keys) and with keys that load its digits unevenly,
-against a stable argsort, bit for bit."""
+"""The radix sort around its tile sizes, its changes of kernel (8192 keys) and of tile size (2^19 keys) and with keys that
+load its digits unevenly, against a stable argsort, bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("kind", ["equal", "descending", "two", "random"])
-@pytest.mark.parametrize("n", [1, 63, 2047, 2048, 2049, 6000, 8193, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, 65 * 8192,
+@pytest.mark.parametrize("n", [1, 63, 1024, 1025, 2047, 2048, 2049, 4097, 8192, 8193, (1 << 19) - 1, 1 << 19, (1 << 19) + 1, 65 * 8192,
                                65 * 8192 + 1])
 def test_sort_around_the_tile_sizes_is_a_stable_sort(gpu_lib, n, kind):
     rng = np.random.default_rng(n)
