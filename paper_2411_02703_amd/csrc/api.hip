@@ -370,7 +370,8 @@ int gs_render_fwd(const gs_frame* f, const gs_opts* o, const gs_images* out, voi
   return GS_OK;
 }
 
-int gs_composite_bwd(const gs_frame* f, const gs_opts* o, const gs_images* fwd, const gs_loss* l, void* stream) {
+// The compositing backward without the sum of the tiles' losses.
+static int composite_bwd(const gs_frame* f, const gs_opts* o, const gs_images* fwd, const gs_loss* l, void* stream) {
   int rc;
   if ((rc = frame_check(f)) || (rc = opts_check(o))) return rc;
   if (!l) return fail(GS_ERR_ARG, "loss is NULL");
@@ -384,19 +385,31 @@ int gs_composite_bwd(const gs_frame* f, const gs_opts* o, const gs_images* fwd, 
     GS_HIP(gs_launch::count_valid(*f, l->tgt_depth, f->max_view_pixels, st), "gs_composite_bwd: valid depth");
   }
   GS_HIP(gs_launch::render_bwd(*f, *o, fwd, *l, st), "gs_composite_bwd");
-  if (l->tgt_rgb) GS_HIP(gs_launch::loss_total(*f, st), "gs_composite_bwd: loss total");
   return GS_OK;
 }
 
-int gs_project_bwd(const gs_params* p, const gs_frame* f, const gs_opts* o, const gs_params* grads, void* stream) {
+int gs_composite_bwd(const gs_frame* f, const gs_opts* o, const gs_images* fwd, const gs_loss* l, void* stream) {
+  int rc;
+  if ((rc = composite_bwd(f, o, fwd, l, stream))) return rc;
+  if (l->tgt_rgb)
+    GS_HIP(gs_launch::loss_total(*f, static_cast<hipStream_t>(stream)), "gs_composite_bwd: loss total");
+  return GS_OK;
+}
+
+static int project_bwd(const gs_params* p, const gs_frame* f, const gs_opts* o, const gs_params* grads,
+                       const gsk::LossSum& ls, void* stream) {
   int rc;
   if ((rc = params_check(p, "params")) || (rc = params_check(grads, "grads")) || (rc = frame_check(f)) ||
       (rc = opts_check(o)))
     return rc;
   if (p->n != f->n || grads->n != f->n || grads->sh_degree != p->sh_degree)
     return fail(GS_ERR_ARG, "params / grads / frame sizes differ");
-  GS_HIP(gs_launch::project_bwd(*p, *f, *o, *grads, static_cast<hipStream_t>(stream)), "gs_project_bwd");
+  GS_HIP(gs_launch::project_bwd(*p, *f, *o, *grads, ls, static_cast<hipStream_t>(stream)), "gs_project_bwd");
   return GS_OK;
+}
+
+int gs_project_bwd(const gs_params* p, const gs_frame* f, const gs_opts* o, const gs_params* grads, void* stream) {
+  return project_bwd(p, f, o, grads, {}, stream);
 }
 
 int gs_render_bwd(const gs_params* p, const gs_frame* f, const gs_opts* o, const gs_images* fwd, const gs_loss* l,
@@ -405,8 +418,8 @@ int gs_render_bwd(const gs_params* p, const gs_frame* f, const gs_opts* o, const
   if ((rc = params_check(p, "params")) || (rc = params_check(grads, "grads")) || (rc = frame_check(f))) return rc;
   if (p->n != f->n || grads->n != f->n || grads->sh_degree != p->sh_degree)
     return fail(GS_ERR_ARG, "params / grads / frame sizes differ");
-  if ((rc = gs_composite_bwd(f, o, fwd, l, stream))) return rc;
-  return gs_project_bwd(p, f, o, grads, stream);
+  if ((rc = composite_bwd(f, o, fwd, l, stream))) return rc;
+  return project_bwd(p, f, o, grads, l->tgt_rgb ? gs_launch::tile_losses(*f) : gsk::LossSum{}, stream);
 }
 
 int gs_ssim(const gs_camera* cams_host, const gs_camera* cams_dev, int32_t V, const float* rgb, const float* tgt,
@@ -508,10 +521,11 @@ int gs_render_bwd_adam(const gs_params* p, const gs_frame* f, const gs_opts* o, 
     return fail(GS_ERR_ARG, "params / moments / frame sizes differ");
   if (grads_out && (grads_out->n != f->n || grads_out->sh_degree != p->sh_degree))
     return fail(GS_ERR_ARG, "grads_out / frame sizes differ");
-  if ((rc = gs_composite_bwd(f, o, fwd, l, stream))) return rc;
-  hipStream_t st = static_cast<hipStream_t>(stream);
-  GS_HIP(gs_launch::adam_prep(*a, f->counters + 1, st), "gs_render_bwd_adam: step");
-  GS_HIP(gs_launch::project_bwd_adam(*p, *f, *o, *m, *v, *a, grads_out, st), "gs_render_bwd_adam");
+  if ((rc = composite_bwd(f, o, fwd, l, stream))) return rc;
+  GS_HIP(gs_launch::project_bwd_adam(*p, *f, *o, *m, *v, *a, grads_out,
+                                     l->tgt_rgb ? gs_launch::tile_losses(*f) : gsk::LossSum{},
+                                     static_cast<hipStream_t>(stream)),
+         "gs_render_bwd_adam");
   return GS_OK;
 }
 

@@ -1132,9 +1132,13 @@ hipError_t clear_project(const gs_frame& f, hipStream_t st) {
 // instance total and the overflow flag.
 hipError_t bin_records(const gs_frame& f, hipStream_t st) {
   const int64_t rcap = f.rec_cap;
-  // kInstSum, kBigCount (and the unused counters), the two sorts' words and the emission's group totals
-  hipError_t e = fill_i32(f.counters + kInstSum, 0,
-                          kFrameCounters - kInstSum + 2 * kSortZero32 + 2 * cdiv(rcap, kGroupItems), st);
+  // the tile ranges; and of the counters the schedule's buckets and all behind them, the two sorts' words and the
+  // emission's group totals
+  constexpr int kFirst = 128;
+  const int64_t nr = 2 * (int64_t)f.n_tiles;
+  const int64_t nc = kFrameCounters - kFirst + 2 * kSortZero32 + 2 * cdiv(rcap, kGroupItems);
+  k_fill2_i32<<<(unsigned)cdiv(nr > nc ? nr : nc, 256), 256, 0, st>>>(f.tile_range, nr, f.counters + kFirst, nc, 0);
+  hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   k_record_list<<<(unsigned)cdiv(f.n, 256), 256, 0, st>>>(f.vis_mask, f.n_rec, f.n_inst, project_totals(f), f.rec_first,
                                                           f.inst_first, reinterpret_cast<const short4*>(f.rect), f.zbits,
@@ -1160,8 +1164,7 @@ hipError_t emit(const gs_frame& f, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The longest-first schedule; its 32 bucket counts (counters[128..160)) were cleared by ranges(), which runs
-// just before it.
+// The longest-first schedule; its 32 bucket counts (counters[128..160)) were cleared by bin_records.
 hipError_t tile_schedule(const gs_frame& f, hipStream_t st) {
   int32_t* cnt = f.counters + 128;
   int32_t* off = f.counters + 160;
@@ -1194,13 +1197,10 @@ hipError_t work_items(const gs_frame& f, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tile ranges; the schedule's bucket counts (counters[128..160)) are cleared in the same launch as the ranges.
+// Tile ranges (cleared by bin_records).
 hipError_t ranges(const gs_frame& f, const uint32_t* keys, int64_t n_sized, const int32_t* count_dev,
                   hipStream_t st) {
-  const int64_t nr = 2 * (int64_t)f.n_tiles;
-  k_fill2_i32<<<(unsigned)cdiv(nr > 32 ? nr : 32, 256), 256, 0, st>>>(f.tile_range, nr, f.counters + 128, 32, 0);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || n_sized <= 0) return e;
+  if (n_sized <= 0) return hipSuccess;
   k_ranges<<<strided_blocks(n_sized), 256, 0, st>>>(keys, count_dev, n_sized, f.capacity,
                                                          reinterpret_cast<int2*>(f.tile_range));
   return hipGetLastError();

@@ -205,13 +205,60 @@ __device__ __forceinline__ int view_of_tile(const gs_camera* __restrict__ cams, 
 
 __device__ __forceinline__ float sgnf(float x) { return x > 0.f ? 1.f : (x < 0.f ? -1.f : 0.f); }
 
+// Unless *skip_flags has the overflow bit (the frame's gradients are then undefined): step <- step + 1;
+// bias = {1 - beta1^step, sqrt(1 - beta2^step)} (computed in double), bias[2] = 0.  Otherwise bias[2] = 1 and
+// nothing else changes; the update kernels then leave every parameter and moment as it is.
+struct AdamPrep {
+  int64_t* step = nullptr;
+  float* bias = nullptr;
+  float b1 = 0.f, b2 = 0.f;
+  const int32_t* skip_flags = nullptr;
+};
+__device__ __forceinline__ void adam_prep_step(const AdamPrep& a) {
+  if (a.skip_flags && (a.skip_flags[0] & GS_FLAG_INSTANCE_OVERFLOW)) {
+    a.bias[2] = 1.f;
+    return;
+  }
+  const int64_t t = a.step[0] + 1;
+  a.step[0] = t;
+  a.bias[0] = (float)(1.0 - pow((double)a.b1, (double)t));
+  a.bias[1] = (float)sqrt(1.0 - pow((double)a.b2, (double)t));
+  a.bias[2] = 0.f;
+}
+
+// loss[0] = sum of part[0, n), by one workgroup (every thread calls it; a power of two of waves, at most 16).
+struct LossSum {
+  const float* part = nullptr;
+  int n = 0;
+  float* loss = nullptr;
+};
+__device__ __forceinline__ void sum_losses(const LossSum& l, float* shared) {
+  const int threads = (int)blockDim.x;
+  float v = 0.f;
+  for (int i = threadIdx.x; i < l.n; i += threads * 8) {
+    float x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) x[k] = i + k * threads < l.n ? l.part[i + k * threads] : 0.f;
+    v += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
+  }
+  v = wave_sum_last(v);
+  if ((threadIdx.x & 63) == 63) shared[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float sum = shared[0];
+    for (int w = 1; w < threads / 64; ++w) sum += shared[w];
+    l.loss[0] = sum;
+  }
+}
+
 }  // namespace gsk
 
 // ------------------------------------------------------------------ host launchers (one per file)
 namespace gs_launch {
 hipError_t project(const gs_params& p, const gs_frame& f, const gs_opts& o, hipStream_t s);
+// Projection backward; with ls.part the loss is summed in passing (see loss_total).
 hipError_t project_bwd(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params& g,
-                       hipStream_t s);
+                       const gsk::LossSum& ls, hipStream_t s);
 size_t scan_scratch_ints(int64_t n);
 // Exclusive scan of in[0, n) into out (in place allowed).
 hipError_t scan_exclusive(const int32_t* in, int32_t* out, int64_t n, int32_t* scratch, hipStream_t s);
@@ -236,7 +283,8 @@ hipError_t work_items(const gs_frame& f, hipStream_t s);
 hipError_t render_fwd(const gs_frame& f, const gs_opts& o, const gs_images& out, hipStream_t s);
 hipError_t count_pairs(const gs_frame& f, const gs_opts& o, unsigned long long* counts, hipStream_t s);
 hipError_t count_valid(const gs_frame& f, const float* tgt_depth, int64_t max_pixels, hipStream_t s);
-// frame loss[0] = sum of the tiles' losses that render_bwd left
+// frame loss[0] = sum of the tiles' losses that render_bwd left (tile_losses)
+gsk::LossSum tile_losses(const gs_frame& f);
 hipError_t loss_total(const gs_frame& f, hipStream_t s);
 hipError_t render_bwd(const gs_frame& f, const gs_opts& o, const gs_images* fwd, const gs_loss& l,
                       hipStream_t s);
@@ -261,9 +309,9 @@ hipError_t spatial_order(const gs_params& p, const gs_params& m, const gs_params
                          const gs_params& om, const gs_params& ov, int32_t* perm_out, int32_t* scratch,
                          hipStream_t s);
 // The step counter and bias corrections of one Adam step (skipped when *skip_flags has the overflow bit).
-hipError_t adam_prep(const gs_adam& a, const int32_t* skip_flags, hipStream_t s);
 // Projection backward fused with Adam: params, m, v updated in place; the gradient is written to grads_out
-// when it is non-NULL.  The step's bias corrections come from adam_prep on the same stream.
+// when it is non-NULL.  The step's count and bias corrections are advanced in passing.
 hipError_t project_bwd_adam(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params& m,
-                            const gs_params& v, const gs_adam& a, const gs_params* grads_out, hipStream_t s);
+                            const gs_params& v, const gs_adam& a, const gs_params* grads_out, const gsk::LossSum& ls,
+                            hipStream_t s);
 }  // namespace gs_launch

@@ -286,11 +286,17 @@ __global__ __launch_bounds__(256) void k_sum_wide(float4* __restrict__ ipart, co
                                                   const short4* __restrict__ rect,
                                                   const int32_t* __restrict__ rec_slot,
                                                   const int32_t* __restrict__ counters, int64_t rcap,
-                                                  int64_t capacity) {
+                                                  int64_t capacity, gsk::LossSum ls, gsk::AdamPrep ap) {
+  if (blockIdx.x == gridDim.x - 1) {  // the last block: what else the frame's backward has to finish, launches saved
+    __shared__ float wsum[4];
+    if (ls.part) gsk::sum_losses(ls, wsum);
+    if (ap.step && threadIdx.x == 64) gsk::adam_prep_step(ap);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int64_t nbig = min((int64_t)counters[198], rcap);
   const int64_t n_stored = min((int64_t)counters[0], capacity);
-  const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+  const int64_t waves = (int64_t)(gridDim.x - 1) * (blockDim.x >> 6);
   for (int64_t b = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); b < nbig; b += waves) {
     const int32_t r = big_rec[b];
     const short4 rc = rect[r];
@@ -686,7 +692,8 @@ hipError_t project(const gs_params& p, const gs_frame& f, const gs_opts& o, hipS
 
 template <bool ADAM>
 static hipError_t project_bwd_launch(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params* gr,
-                                     const AdamArgs& ad, hipStream_t st) {
+                                     const AdamArgs& ad, const gsk::LossSum& ls, const gsk::AdamPrep& ap,
+                                     hipStream_t st) {
   const int threads = 256;
   const int blocks = (int)((p.n + threads - 1) / threads);
   const DevOpts op = gsk::dev_opts(o);
@@ -697,8 +704,8 @@ static hipError_t project_bwd_launch(const gs_params& p, const gs_frame& f, cons
   float* gq = gr ? gr->quats : nullptr;
   float* go = gr ? gr->opacity : nullptr;
   float* gsh = gr ? gr->sh : nullptr;
-  k_sum_wide<<<1024, 256, 0, st>>>(reinterpret_cast<float4*>(f.ipart), f.big_rec, rect, f.rec_slot, f.counters,
-                                   f.rec_cap, f.capacity);
+  k_sum_wide<<<1024 + 1, 256, 0, st>>>(reinterpret_cast<float4*>(f.ipart), f.big_rec, rect, f.rec_slot, f.counters,
+                                   f.rec_cap, f.capacity, ls, ap);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 #define GS_PB(D)                                                                                              \
@@ -715,13 +722,15 @@ static hipError_t project_bwd_launch(const gs_params& p, const gs_frame& f, cons
   return hipGetLastError();
 }
 
-hipError_t project_bwd(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params& gr, hipStream_t st) {
+hipError_t project_bwd(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params& gr,
+                       const gsk::LossSum& ls, hipStream_t st) {
   AdamArgs none{};
-  return project_bwd_launch<false>(p, f, o, &gr, none, st);
+  return project_bwd_launch<false>(p, f, o, &gr, none, ls, {}, st);
 }
 
 hipError_t project_bwd_adam(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params& m,
-                            const gs_params& v, const gs_adam& a, const gs_params* grads_out, hipStream_t st) {
+                            const gs_params& v, const gs_adam& a, const gs_params* grads_out, const gsk::LossSum& ls,
+                            hipStream_t st) {
   AdamArgs ad;
   ad.m_means = m.means; ad.m_scales = m.log_scales; ad.m_quats = m.quats; ad.m_opac = m.opacity; ad.m_sh = m.sh;
   ad.v_means = v.means; ad.v_scales = v.log_scales; ad.v_quats = v.quats; ad.v_opac = v.opacity; ad.v_sh = v.sh;
@@ -731,7 +740,8 @@ hipError_t project_bwd_adam(const gs_params& p, const gs_frame& f, const gs_opts
   ad.eps = a.eps;
   ad.bias = a.bias;
   ad.sparse = (a.flags & GS_ADAM_SPARSE) ? 1 : 0;
-  return project_bwd_launch<true>(p, f, o, grads_out, ad, st);
+  return project_bwd_launch<true>(p, f, o, grads_out, ad, ls,
+                                  {a.step, a.bias, a.beta1, a.beta2, f.counters + 1}, st);
 }
 
 }  // namespace gs_launch

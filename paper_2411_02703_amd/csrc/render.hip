@@ -557,24 +557,9 @@ __device__ __forceinline__ void store_loss(const TileCtx& t, const BwdArgs& a, i
   }
 }
 
-// loss[0] = sum of part[0, n), by one workgroup.
-__global__ __launch_bounds__(1024) void k_loss_total(const float* __restrict__ part, int n, float* __restrict__ loss) {
+__global__ __launch_bounds__(1024) void k_loss_total(gsk::LossSum l) {
   __shared__ float wsum[16];
-  float v = 0.f;
-  for (int i = threadIdx.x; i < n; i += 1024 * 8) {
-    float x[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) x[k] = i + k * 1024 < n ? part[i + k * 1024] : 0.f;
-    v += ((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]));
-  }
-  v = gsk::wave_sum_last(v);
-  if ((threadIdx.x & 63) == 63) wsum[threadIdx.x >> 6] = v;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    float sum = wsum[0];
-    for (int w = 1; w < 16; ++w) sum += wsum[w];
-    loss[0] = sum;
-  }
+  gsk::sum_losses(l, wsum);
 }
 
 // Partial slot of the instance of a record (first slot and pixel rectangle) in the tile at pixel origin (tx0, ty0): the
@@ -1572,8 +1557,10 @@ static float* loss_parts(const gs_frame& f) {
   return f.seg + (size_t)gsk::seg_slots(f.n_tiles, f.seg_cap) * 6 * f.tile_w * f.tile_h;
 }
 
+gsk::LossSum tile_losses(const gs_frame& f) { return {loss_parts(f), f.n_tiles, f.loss}; }
+
 hipError_t loss_total(const gs_frame& f, hipStream_t st) {
-  k_loss_total<<<1, 1024, 0, st>>>(loss_parts(f), f.n_tiles, f.loss);
+  k_loss_total<<<1, 1024, 0, st>>>(tile_losses(f));
   return hipGetLastError();
 }
 
