@@ -364,8 +364,10 @@ __global__ __launch_bounds__(256) void k_project_bwd(float* __restrict__ means, 
   constexpr int FP = F + 1;  // LDS row stride (odd, so a lane per row hits distinct banks)
   // The SH gradient of a lane's Gaussian is summed in its LDS row (FP floats; with ADAM the last one flags a
   // Gaussian that takes no step) rather than in registers, which halves the kernel's register footprint; with
-  // ADAM the wave then steps its 64 rows in coalesced runs of parameters and moments instead of one 4F-byte
-  // row per lane.
+  // ADAM the wave then steps its 64 rows in coalesced runs of 16-byte words of parameters and moments instead of one
+  // 4F-byte row per lane.  What bounds the kernel is HBM with one view (1M Gaussians of degree 3: 1.3 GB in 366 us; 384 with
+  // 4-byte words) and with many views the arithmetic per record, at three waves a SIMD (16-byte words in the LDS rows too
+  // made 24 views slower: 969 -> 1105 us).
   __shared__ float sbuf[4 * 64 * FP];
   const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int lane = threadIdx.x & 63;
@@ -585,34 +587,69 @@ __global__ __launch_bounds__(256) void k_project_bwd(float* __restrict__ means, 
     // others lr[5]
     wb[lane * FP + F] = step ? 0.f : 1.f;
     __syncthreads();
-    // U elements per lane at a time: all their loads are issued before the first is used, so a lane waits
-    // for memory once per U elements rather than once per element
-    constexpr int U = 8;
     const float s4 = ad.lr[4] / bc1, s5 = ad.lr[5] / bc1;
     const int total = nw * F;
-    for (int e0 = lane; e0 < total; e0 += 64 * U) {
-      float pv[U], mm[U], vv[U];
-      bool on[U];
+    auto off = [&](int r) { return wb[r * FP + F] != 0.f; };
+    auto step_one = [&](int e) {
+      const int r = e / F, c = e - r * F;
+      if (off(r)) return;
+      const int64_t idx = g0 * F + e;
+      float pv = sh[idx], mm = ad.m_sh[idx], vv = ad.v_sh[idx];
+      adam_one(pv, mm, vv, wb[r * FP + c], c < 3 ? s4 : s5, b1, b2, eps, bc2s);
+      sh[idx] = pv;
+      ad.m_sh[idx] = mm;
+      ad.v_sh[idx] = vv;
+    };
+    if (((reinterpret_cast<uintptr_t>(sh) | reinterpret_cast<uintptr_t>(ad.m_sh) | reinterpret_cast<uintptr_t>(ad.v_sh)) &
+         15) != 0) {  // arrays that do not start at a 16-byte word
+      for (int e = lane; e < total; e += 64) step_one(e);
+    } else {
+      // U words per lane at a time: all their loads are issued before the first is used, so a lane waits for memory once
+      // per U words.  A word of rows of 27 floats may reach into the next row.
+      constexpr int U = 4;
+      const int words = total / 4;
+      float4* p4 = reinterpret_cast<float4*>(sh + g0 * F);  // (g0 is a multiple of 64)
+      float4* m4 = reinterpret_cast<float4*>(ad.m_sh + g0 * F);
+      float4* v4 = reinterpret_cast<float4*>(ad.v_sh + g0 * F);
+      for (int w0 = lane; w0 < words; w0 += 64 * U) {
+        float4 pv[U], mm[U], vv[U];
+        bool on[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int e = e0 + 64 * u;
-        on[u] = e < total && wb[(e / F) * FP + F] == 0.f;
-        const int64_t idx = g0 * F + (on[u] ? e : 0);
-        pv[u] = sh[idx];
-        mm[u] = ad.m_sh[idx];
-        vv[u] = ad.v_sh[idx];
-      }
+        for (int u = 0; u < U; ++u) {
+          const int w = w0 + 64 * u;
+          on[u] = w < words && (!off(4 * w / F) || (F % 4 != 0 && !off((4 * w + 3) / F)));
+          const int at = on[u] ? w : 0;
+          pv[u] = p4[at];
+          mm[u] = m4[at];
+          vv[u] = v4[at];
+        }
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (!on[u]) continue;
-        const int e = e0 + 64 * u;
-        const int r = e / F, c = e - r * F;
-        const int64_t idx = g0 * F + e;
-        adam_one(pv[u], mm[u], vv[u], wb[r * FP + c], c < 3 ? s4 : s5, b1, b2, eps, bc2s);
-        sh[idx] = pv[u];
-        ad.m_sh[idx] = mm[u];
-        ad.v_sh[idx] = vv[u];
+        for (int u = 0; u < U; ++u) {
+          if (!on[u]) continue;
+          const int w = w0 + 64 * u;
+          const int r0 = 4 * w / F, c0 = 4 * w - r0 * F;
+          float* pe = &pv[u].x;
+          float* me = &mm[u].x;
+          float* ve = &vv[u].x;
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            int r = r0, c = c0 + j;
+            if (F % 4 != 0) {
+              // (rows of 3 floats: a word may reach over two of them)
+              while (c >= F) {
+                c -= F;
+                ++r;
+              }
+              if (off(r)) continue;
+            }
+            adam_one(pe[j], me[j], ve[j], wb[r * FP + c], c < 3 ? s4 : s5, b1, b2, eps, bc2s);
+          }
+          p4[w] = pv[u];
+          m4[w] = mm[u];
+          v4[w] = vv[u];
+        }
       }
+      if (lane < total % 4) step_one(4 * words + lane);
     }
   }
   if (!step) return;
