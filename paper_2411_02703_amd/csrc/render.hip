@@ -1001,11 +1001,11 @@ __device__ __forceinline__ void for_items(int count, int32_t* ctr, Body body) {
   }
 }
 
-// A whole tile of fewer records than this has its forward in the backward's block instead of k_bwd_sums: the sums that
-// k_bwd_sums leaves behind (20 B written and read per pixel) cost as much as a short list's sweep.  A step over 16.5 k
-// tiles of 13 records: 439 us with every tile's forward in k_bwd_sums, 434 us with this rule at 16, 32 or 64; a
-// keyframe of long lists: 1649, 1651, 1651 and 1653 us.
-constexpr int kOwnForward = 32;
+// A whole tile of 1 to kOwnForward - 1 records has its forward in the backward's block instead of k_bwd_sums: the sums
+// that k_bwd_sums leaves behind (20 B written and read per pixel) cost as much as a very short list's sweep, which the
+// backward's kernel runs at half the waves.  Both kernels together with the line at 2, 8 and 32: 28 k tiles of 32x8 with
+// some 12 records each 406, 409 and 422 us; 16.5 k tiles of 16x8 with 13 143, 146 and 147; 24 views 3022, 3007 and 2993.
+constexpr int kOwnForward = 8;
 
 // Step 1 of the backward: segments of the split tiles run segment_sums; whole tiles run the forward sweep up to the
 // upstream gradient and leave it (g and S, six floats a pixel) in the segment state's slot of their work item (with
@@ -1025,9 +1025,10 @@ __global__ __launch_bounds__(TW * TH, 6) void k_bwd_sums(const float4* __restric
     tile_at<G>(cams, V, it.x, t);
     if (it.z >= 0) {
       segment_sums<G>(s, rec, vals, range[it.x], it, t, op, g);
-    } else if (const int2 rg = range[it.x]; !HAVE_FWD && rg.y - rg.x >= kOwnForward) {
+    } else if (const int2 rg = range[it.x]; !HAVE_FWD && (rg.x >= rg.y || rg.y - rg.x >= kOwnForward)) {
       float v[6];
       tile_upstream<G, false, LOSS>(s, rec, vals, rg, t, op, a, it.w, v[0], v[1], v[2], v[3], v[4], v[5]);
+      if (rg.x >= rg.y) return;  // an empty tile: its loss is in
       float* o = g.seg + (size_t)b * 6 * G::NT + threadIdx.x;
 #pragma unroll
       for (int i = 0; i < 6; ++i)
@@ -1268,6 +1269,7 @@ __global__ __launch_bounds__(TW * TH, 4) void k_bwd_main(const float4* __restric
   for_items<PERSIST>(g.counters[192], ctr, [&](int b) {
     const int4 it = g.items[b];
     int2 rg = range[it.x];
+    if (!HAVE_FWD && g.whole && rg.x >= rg.y) return;  // an empty tile, done by k_bwd_sums
     TileCtx t;
     tile_at<G>(cams, V, it.x, t);
     bool live = t.inside;
@@ -1359,7 +1361,11 @@ __global__ __launch_bounds__(TW * TH) void k_count_pairs(const float4* __restric
 }
 
 // Valid LiDAR-depth pixels per view: grid-stride per view, one atomic per block.
-__global__ __launch_bounds__(256) void k_count_valid(const float* __restrict__ tgt_depth,
+// (Blocks of 1024 threads: the blocks' atomics on one cache line queue at about 5 ns each, 19 of 26 us over 24 views in
+// blocks of 256.)
+constexpr int kValidThreads = 1024;
+
+__global__ __launch_bounds__(kValidThreads) void k_count_valid(const float* __restrict__ tgt_depth,
                                                      const gs_camera* __restrict__ cams,
                                                      int32_t* __restrict__ n_valid) {
   __shared__ int sh;
@@ -1567,13 +1573,13 @@ hipError_t loss_total(const gs_frame& f, hipStream_t st) {
 hipError_t count_valid(const gs_frame& f, const float* tgt_depth, int64_t max_pixels, hipStream_t st) {
   hipError_t e = fill_i32(f.counters + 2, 0, f.n_views, st);
   if (e != hipSuccess) return e;
-  // eight loads a thread, or up to 32 where the views together make more than 512 blocks anyway
-  int64_t bx = (max_pixels + 256 * 32 - 1) / (256 * 32);
-  const int64_t wide = (max_pixels + 256 * 8 - 1) / (256 * 8), most = 512 / f.n_views;
+  // eight loads a thread, or up to 32 where the views together make more than 128 blocks anyway
+  int64_t bx = (max_pixels + kValidThreads * 32 - 1) / (kValidThreads * 32);
+  const int64_t wide = (max_pixels + kValidThreads * 8 - 1) / (kValidThreads * 8), most = 128 / f.n_views;
   if (bx < most) bx = wide < most ? wide : most;
   if (bx < 1) bx = 1;
   dim3 grid((unsigned)bx, (unsigned)f.n_views);
-  k_count_valid<<<grid, 256, 0, st>>>(tgt_depth, f.cams, f.counters + 2);
+  k_count_valid<<<grid, kValidThreads, 0, st>>>(tgt_depth, f.cams, f.counters + 2);
   return hipGetLastError();
 }
 
