@@ -731,7 +731,8 @@ template <bool ADAM>
 static hipError_t project_bwd_launch(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params* gr,
                                      const AdamArgs& ad, const gsk::LossSum& ls, const gsk::AdamPrep& ap,
                                      hipStream_t st) {
-  const int threads = 256;
+  // few Gaussians: a wave a block, so that they spread over the CUs (2915 Gaussians of degree 3 in 14 views: 85 -> 77 us)
+  const int threads = p.n <= 32768 ? 64 : 256;
   const int blocks = (int)((p.n + threads - 1) / threads);
   const DevOpts op = gsk::dev_opts(o);
   const auto* ip = reinterpret_cast<const float4*>(f.ipart);
