@@ -1,9 +1,9 @@
-"""Pick the tile shape, records staged per thread, block width of the lock-step walk and depth-segment length
-of the batched step by measured replay time.
+"""Pick the tile shape, records staged per thread and depth-segment length of the batched step by measured replay
+time.
 
 Every candidate computes the same forward bit for bit (the per-pair arithmetic is fixed and records are
 culled only where they provably do not contribute) and the same gradients up to the order of the float
-atomic additions (and, for the segment length, the FP32 association of the transmittance product), so the
+additions (and, for the segment length, the FP32 association of the transmittance product), so the
 choice changes speed only.  Results are cached in a JSON file keyed by the GPU
 architecture, the resolution class, the Gaussian-count band and the SH degree.
 """
@@ -19,12 +19,12 @@ import torch
 
 from . import binding as B
 
-# (tile_w, tile_h, records staged per thread, block width of the lock-step walk, depth-segment length;
+# (tile_w, tile_h, records staged per thread, block width (4: the compositing has no other), depth-segment length;
 # -1 = never split).  The first is the default: another candidate is chosen only if it is faster by more than
 # TIE (measurement noise would otherwise flip between near-equal ones from run to run).
 CANDIDATES: List[Tuple[int, int, int, int, int]] = [
-    (16, 8, 1, 4, 512), (16, 16, 1, 4, 512), (16, 16, 1, 4, 1024), (16, 8, 1, 4, 1024), (16, 8, 1, 8, 512),
-    (16, 8, 2, 4, 512), (8, 8, 1, 4, 512), (32, 8, 1, 4, 512), (16, 16, 1, 8, -1), (16, 16, 1, 2, 512)]
+    (16, 8, 1, 4, 512), (16, 16, 1, 4, 512), (16, 16, 1, 4, 1024), (16, 8, 1, 4, 1024), (16, 8, 2, 4, 512),
+    (8, 8, 1, 4, 512), (32, 8, 1, 4, 512), (16, 16, 1, 4, -1)]
 TIE = 0.02
 
 _CACHE = os.environ.get("GS_AUTOTUNE_CACHE",
