@@ -379,7 +379,7 @@ __global__ __launch_bounds__(kSortThreads, sizeof(KeyT) == 4 ? 8 : 4) void k_sor
 
 // A sort of at most kBlockSort keys: every pass in one block, through its LDS, where the launches of a kernel per pass were
 // the cost.  Four passes over 300 keys take 17 us here and 31 in launches of their own, over 2000 21 and 35, over 6000 39
-// and 41, over 8192 41 and 41 (and a capacity is seldom full).
+// and 41, over 8192 41 and 41 (and a capacity is seldom full).  Input and output may be the same arrays.
 constexpr int kBlockSort = kSortThreads * kLargeItems;
 
 template <class KeyT>
@@ -391,9 +391,8 @@ struct BlockStage {
 };
 
 template <class KeyT, int ITEMS>
-__device__ __forceinline__ void sort_block(BlockStage<KeyT>& s, const KeyT* __restrict__ kin,
-                                           const int32_t* __restrict__ vin, KeyT* __restrict__ kout,
-                                           int32_t* __restrict__ vout, int n, int passes) {
+__device__ __forceinline__ void sort_block(BlockStage<KeyT>& s, const KeyT* kin, const int32_t* vin, KeyT* kout,
+                                           int32_t* vout, int n, int passes) {
   constexpr int WAVES = kSortThreads / 64;
   const int tid = threadIdx.x, wave = tid >> 6, i0 = wave * 64 * ITEMS + __lane_id();
   KeyT key[ITEMS];
@@ -457,10 +456,9 @@ __device__ __forceinline__ void sort_block(BlockStage<KeyT>& s, const KeyT* __re
 }
 
 template <class KeyT>
-__global__ __launch_bounds__(kSortThreads) void k_sort_block(const KeyT* __restrict__ kin,
-                                                             const int32_t* __restrict__ vin, KeyT* kout, int32_t* vout,
-                                                             const int32_t* __restrict__ count_dev, int64_t n_sized,
-                                                             int64_t cap, int passes) {
+__global__ __launch_bounds__(kSortThreads) void k_sort_block(const KeyT* kin, const int32_t* vin, KeyT* kout,
+                                                             int32_t* vout, const int32_t* __restrict__ count_dev,
+                                                             int64_t n_sized, int64_t cap, int passes) {
   __shared__ BlockStage<KeyT> s;
   const int n = (int)sort_count(count_dev, n_sized, cap);
   if (n <= kSortThreads) sort_block<KeyT, 1>(s, kin, vin, kout, vout, n, passes);
