@@ -685,11 +685,17 @@ __device__ __forceinline__ bool any_live(const f32x4& T, const DevOpts& op) {
 //   * A record's ten sums over the block's rows are reduced and spread over the rows (ten values by eight lane swaps),
 //     and added to the wave's own LDS sums by plain reads and writes, once per sixteen records: LDS float atomics
 //     take about two cycles a lane and had kept the LDS busy for 85% of the kernel's time.
+//   * A pair that does not contribute has alpha = w = 0 and adds 0 times what its pixel's upstream gradient gives, which
+//     is 0 as long as that is finite.  A block with a pixel whose gradient is not, or is so large that a product of it
+//     might not be (far), leaves such pairs out instead: what is not finite reaches the records that contribute at its
+//     pixel, no others.
 // Returns whether a pixel of the blocks that this wave took is still live.
 // What bounds it is issue.
+constexpr float kFarGradient = 1e18f;
+
 template <class G, bool VIS, bool WHOLE>
 __device__ __forceinline__ void backward_block(BwdStage<G>& s, const TileCtx& t, const DevOpts& op, int blk,
-                                               const uint8_t* list, int n, f32x4& T) {
+                                               const uint8_t* list, int n, bool far, f32x4& T) {
   const int r = t.lane & 15, k = t.lane >> 4, p0 = blk * 16, sub = blk >> 2;
   f32x4 R = *reinterpret_cast<const f32x4*>(&s.R[p0 + 4 * k]);
   f32x4 gv = {0.f, 0.f, 0.f, 0.f};
@@ -748,14 +754,32 @@ __device__ __forceinline__ void backward_block(BwdStage<G>& s, const TileCtx& t,
 #pragma unroll
     for (int i = 0; i < 4; ++i) pre[i] += gsk::dpp_f<0x118>(pre[i]);
     f32x4 col = {0.f, 0.f, 0.f, 0.f};
+    if (WHOLE && far) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) col = __builtin_amdgcn_mfma_f32_4x4x1f32(gw[i], w[i], col, 0, 0, 0);
+      for (int c = 0; c < 4; ++c) {
+        const f32x4 gc = *reinterpret_cast<const f32x4*>(&s.g[c][p0 + 4 * k]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) col[c] += am[i] > 0.f ? gc[i] * w[i] : 0.f;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) col = __builtin_amdgcn_mfma_f32_4x4x1f32(gw[i], w[i], col, 0, 0, 0);
+    }
+    float dalpha[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float Rn = R[i] - pre[i];
       R[i] = gsk::dpp_f<0x15F>(Rn);
-      const float dalpha = x[i] * q[i] - Rn * __builtin_amdgcn_rcpf(om[i]);
-      const float dq = (WHOLE && clamped[i] ? 0.f : am[i]) * dalpha;  // a clamped alpha passes no gradient
+      dalpha[i] = x[i] * q[i] - Rn * __builtin_amdgcn_rcpf(om[i]);
+      if (WHOLE && clamped[i]) am[i] = 0.f;  // a clamped alpha passes no gradient
+    }
+    if (WHOLE && far) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) dalpha[i] = am[i] > 0.f ? dalpha[i] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float dq = am[i] * dalpha[i];
       const float dqx = dq * dx[i];
       s0 = i ? s0 + dq : dq;
       sx = i ? sx + dqx : dqx;
@@ -786,6 +810,10 @@ __device__ __forceinline__ bool backward_round(BwdStage<G>& s, const TileCtx& t,
   for (; blk < G::NB; blk = __builtin_amdgcn_readfirstlane(t.lane == 0 ? atomicAdd(&s.next, 1) : 0)) {
     f32x4 T = *reinterpret_cast<const f32x4*>(&s.T[blk * 16 + 4 * (t.lane >> 4)]);
     if (!any_live(T, op)) continue;
+    const int px = blk * 16 + (t.lane & 15);
+    bool far = !(fabsf(s.g[t.lane >> 4][px]) < kFarGradient && fabsf(s.R[px]) < kFarGradient);
+    if (VIS) far |= !(fabsf(s.gv[px]) < kFarGradient);
+    far = __builtin_amdgcn_ballot_w64(far) != 0;
     int n = 0;
     uint64_t whole = 0;
 #pragma unroll
@@ -802,10 +830,10 @@ __device__ __forceinline__ bool backward_round(BwdStage<G>& s, const TileCtx& t,
     }
     if (t.lane < 16) list[n + t.lane] = (uint8_t)G::BATCH;  // the empty record
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");  // the list is read by other lanes of this wave only
-    if (whole)
-      backward_block<G, VIS, true>(s, t, op, blk, list, n, T);
+    if (whole || far)
+      backward_block<G, VIS, true>(s, t, op, blk, list, n, far, T);
     else
-      backward_block<G, VIS, false>(s, t, op, blk, list, n, T);
+      backward_block<G, VIS, false>(s, t, op, blk, list, n, false, T);
     any |= any_live(T, op);
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
   }

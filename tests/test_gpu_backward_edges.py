@@ -59,3 +59,54 @@ def test_the_backward_stops_at_the_forwards_pair(gpu_lib, n, tile):
                                 g_vis=torch.zeros_like(vis))
                 hit = (model.g["sh"].view(n, -1) != 0).all(dim=1).cpu().numpy()
                 assert hit[:count].all() and not hit[count:].any(), (k, count, np.flatnonzero(hit))
+
+
+@pytest.mark.parametrize("field", ["g_rgb", "g_depth", "g_vis"])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), -float("inf"), 3e38])
+@pytest.mark.parametrize("tile,seg", [((16, 16), -1), ((8, 8), -1), ((16, 8), 64)])
+def test_a_gradient_that_is_not_finite_reaches_the_contributing_records_only(gpu_lib, tile, seg, value, field):
+    """Records whose pixels all have ordinary gradients get the gradient that they get with 0 at the other pixels (up to
+    the order of the float sums), whatever stands there."""
+    n, w, h = 400, 40, 24
+    rng = np.random.default_rng(5)
+    sc = scenes.random_scene(77, n, w, h, log_scale_mu=-2.4, zrange=(3.0, 6.0))
+    sc.sh[:] = rng.uniform(0.2, 1.0, sc.sh.shape)  # (no clamped colour)
+    sc.opacity[: n // 8] = 6.0  # clamped alphas, which take the other form of the walk
+    model = GaussianModel(sc.params(), 0)
+    fr = _frame(model, sc.cams, tile_w=tile[0], tile_h=tile[1], seg_len=seg)
+    img = fr.empty_images()
+    B.gs_render_fwd(fr, *img)
+
+    def grads(fwd, **g):
+        model.zero_grad()
+        B.gs_render_bwd(model.ps, fr, fwd, model.gs, **g)
+        return {k: v.view(n, -1).cpu().numpy().astype(np.float64) for k, v in model.g.items()}
+
+    bad = [5 * w + 7, 17 * w + 30, 23 * w + 39]
+    base = dict(g_rgb=torch.randn(3 * w * h, device="cuda"), g_depth=torch.randn(w * h, device="cuda"),
+                g_vis=torch.randn(w * h, device="cuda"))
+    zero = {k: torch.zeros_like(v) for k, v in base.items()}
+    one = zero["g_rgb"].clone()
+    for c in range(3):
+        for p in bad:
+            one[c * w * h + p] = 1.0
+    touched = (grads(img, **dict(zero, g_rgb=one))["sh"] != 0).any(axis=1)
+    assert 0 < touched.sum() < n // 2
+    clean = {k: v.clone() for k, v in base.items()}
+    for k, v in clean.items():
+        for p in bad:
+            v.view(-1, w * h)[:, p] = 0.0
+    dirty = {k: v.clone() for k, v in clean.items()}
+    for p in bad:
+        dirty[field].view(-1, w * h)[:, p] = value
+    for fwd in (img, None):
+        print("not finite", tile, seg, value, field, fwd is None, flush=True)
+        want, got = grads(fwd, **clean), grads(fwd, **dirty)
+        for k in want:
+            a, b = want[k][~touched], got[k][~touched]
+            rms = np.sqrt((want[k] ** 2).mean())
+            assert np.isfinite(b).all(), (k, int((~np.isfinite(b)).any(axis=1).sum()))
+            assert np.abs(a - b).max() <= 1e-4 * rms, k
+        if not np.isfinite(value):
+            reached = np.any([~np.isfinite(got[k]).all(axis=1) for k in got], axis=0)
+            assert reached[touched & (sc.opacity < 4.0)].all()
