@@ -397,13 +397,16 @@ int gs_sort_pairs(uint64_t* keys, int32_t* vals, uint64_t* keys_tmp, int32_t* va
                   int32_t key_bits, int32_t* scratch, void* stream);
 
 /* The same sort for callers that cannot allocate device memory (code under HIP graph capture, tight serving
- * loops, harnesses that forbid hipMalloc): the ping-pong buffers and histograms live in a static device array
+ * loops, harnesses that forbid hipMalloc): the ping-pong buffers and sort states live in a static device array
  * of the library (about 13.6 MB, one copy per GPU, held until the process ends), so the caller passes only
  * keys/vals, sorted in place.  n is limited to gs_sort_static_max() pairs (2^20); larger n returns
  * GS_ERR_ARG before anything is enqueued.  The call allocates nothing.  `stream` must belong to the current
  * device.  Every call on a GPU shares that GPU's array: calls that overlap on one GPU (on different streams,
- * or from several threads) race and must be serialised by the caller.  No part of the array needs clearing
- * between calls (every pass rewrites what it reads). */
+ * or from several threads) race and must be serialised by the caller.  Where they are not, the pairs of either
+ * call end in an undefined order, some of them more than once and some not at all; a pass that then waits for
+ * another's counts in vain goes on after about a second, and nothing outside the arrays is written.  The same holds
+ * for gs_sort_pairs calls that share scratch.  No part of the array needs clearing between calls (every call clears
+ * what it reads). */
 int64_t gs_sort_static_max(void);
 int gs_sort_pairs_static(uint64_t* keys, int32_t* vals, int64_t n, int32_t key_bits, void* stream);
 

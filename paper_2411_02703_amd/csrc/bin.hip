@@ -13,6 +13,7 @@
 // record's tiles row by row: each record's first slot is written here, in Gaussian order, so that the projection
 // backward reads one contiguous run per Gaussian.
 #include "common.h"
+#include "chain.h"
 
 namespace {
 
@@ -129,9 +130,7 @@ __device__ __forceinline__ int64_t sort_count(const int32_t* count_dev, int64_t 
 constexpr int kCopies = 8;
 constexpr int kSortZero32 = kCopies * 4 * 256 + 64, kSortZero64 = kCopies * 8 * 256 + 64;
 
-// A tile's state for one digit: 0 so far absent, 1 + the count of its keys, or with the top bit the count of its and all
-// earlier tiles' keys (below 2^31, as the sizes are).  Written and read whole, so that no other ordering is needed.
-constexpr uint32_t kWhole = 0x80000000u;
+using gsk::kWhole;  // (chain.h describes the states)
 __device__ __forceinline__ void put_state(uint32_t* p, uint32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -203,7 +202,7 @@ __global__ __launch_bounds__(kDigitThreads) void k_sort_digits(const KeyT* __res
 
 // Stable scatter of one 8-bit digit.  Tiles are taken in the order of a ticket counter, so that every tile before a
 // running block's belongs to a block that runs or has finished: the waits below end, because a block publishes its own
-// counts before it waits.  Each wave ranks its keys (ITEMS rounds of 64) with ballot-based digit matching, the block
+// counts before it waits (and where another sort meddles, after kChainLooks looks, with every place in range).  Each wave ranks its keys (ITEMS rounds of 64) with ballot-based digit matching, the block
 // orders them in LDS (digit-major, stable), adds up the earlier tiles' counts (a digit per thread, kLook tiles' words in
 // flight) and writes runs to their global places, first keys, then values through the same LDS.  state: this pass's
 // states, cleared before; next: the following pass's, cleared here.
@@ -313,20 +312,8 @@ __device__ __forceinline__ void scatter_tile(SortStage<KeyT>& s, const KeyT* __r
   if (tid < 256) {
     uint32_t before = 0;
     if (tile > 0) {
-      for (int j = tile - 1;;) {
-        uint32_t v[kLook];
-#pragma unroll
-        for (int i = 0; i < kLook; ++i) v[i] = get_state(state + (int64_t)max(j - i, 0) * 256 + tid);
-        bool done = false;
-#pragma unroll
-        for (int i = 0; i < kLook; ++i) {
-          if (done || v[i] == 0) break;  // (absent so far: read again from here)
-          done = (v[i] & kWhole) != 0;
-          before += done ? v[i] & ~kWhole : v[i] - 1u;
-          --j;
-        }
-        if (done) break;
-      }
+      before = gsk::keys_before<kLook>(tile, gsk::kChainLooks,
+                                       [&](int j) { return get_state(state + (int64_t)j * 256 + tid); });
       put_state(my_state, kWhole | (before + (uint32_t)total));
     }
     gofs[tid] = in_d + (int)before - in_c;
@@ -338,7 +325,7 @@ __device__ __forceinline__ void scatter_tile(SortStage<KeyT>& s, const KeyT* __r
     const int p = k * THREADS + tid;
     if (p < nvalid) {
       const KeyT kk = sk[p];
-      out[k] = gofs[(int)((kk >> shift) & 255u)] + p;
+      out[k] = (int)gsk::key_place((uint32_t)gofs[(int)((kk >> shift) & 255u)], p, (uint32_t)n);
       kout[out[k]] = kk;
     }
   }
@@ -363,7 +350,10 @@ __global__ __launch_bounds__(kSortThreads, sizeof(KeyT) == 4 ? 8 : 4) void k_sor
   const int64_t n = sort_count(count_dev, n_sized, cap);
   if ((int64_t)blockIdx.x * sort_tile(n) >= n) return;  // (as many blocks as tiles go on)
   const int tid = threadIdx.x;
-  if (tid == 0) s.tile = atomicAdd(digits + kCopies * 256 * passes + pass, 1);
+  if (tid == 0) {  // (the minimum: where another sort meddles with the tickets, the tile is one of this sort's all the same)
+    const uint32_t ticket = (uint32_t)atomicAdd(digits + kCopies * 256 * passes + pass, 1);
+    s.tile = (int)min(ticket, (uint32_t)((n - 1) / sort_tile(n)));
+  }
   for (int i = tid; i < kSortThreads / 64 * 256; i += kSortThreads) (&s.cnt[0][0])[i] = 0;
   int dc = 0;  // the digit's keys
   if (tid < 256) {
