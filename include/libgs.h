@@ -183,8 +183,8 @@ typedef struct gs_frame {
   int32_t* seg_first;   /* [n_tiles]: exclusive scan of seg_count = first work item of that tile */
   int32_t* items;       /* [item_cap][4]: work items of the compositing calls, split tiles first:
                            {tile, segment, first slot of the tile or -1, schedule position} */
-  float* seg;           /* [seg_cap, in frames of 2048 tiles or more item_cap][6][tile_w * tile_h]: per-segment pixel
-                           state of split tiles; in the backward of such frames also the upstream gradient of whole
+  float* seg;           /* [seg_cap, in frames of 2048 tiles or more that split lists item_cap][6][tile_w * tile_h]:
+                           per-segment pixel state of split tiles; in the backward of such frames also the upstream gradient of whole
                            tiles; and behind it [n_tiles] each tile's loss */
   float* split;         /* [long_cap][12][tile_w * tile_h]: per-pixel stop state and upstream gradient */
   float* loss;          /* [64]: loss[0] the loss value written by gs_render_bwd in loss mode */

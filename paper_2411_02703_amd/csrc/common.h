@@ -18,8 +18,10 @@ constexpr int kLossSlots = 32;
 // 20 us in one kernel, 11 + 21 us in two).
 constexpr int kWholeTiles = 2048;
 
-// Slots of a frame's segment state.
-inline int seg_slots(int n_tiles, int seg_cap) { return n_tiles >= kWholeTiles ? n_tiles + seg_cap : seg_cap; }
+// Slots of a frame's segment state (none where lists are never split, seg_cap = 0: k_render_bwd keeps no state).
+inline int seg_slots(int n_tiles, int seg_cap) {
+  return seg_cap > 0 && n_tiles >= kWholeTiles ? n_tiles + seg_cap : seg_cap;
+}
 
 // Options as the kernels see them (passed by value).
 struct DevOpts {
