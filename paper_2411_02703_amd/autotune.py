@@ -5,10 +5,12 @@ Every candidate computes the same forward bit for bit (the per-pair arithmetic i
 culled only where they provably do not contribute) and the same gradients up to the order of the float
 additions (and, for the segment length, the FP32 association of the transmittance product), so the
 choice changes speed only.  Results are cached in a JSON file keyed by the GPU
-architecture, the resolution class, the Gaussian-count band and the SH degree.
+architecture, the resolution class, the Gaussian-count band and the SH degree; an entry holds for the library and the
+candidates that it was measured with.
 """
 from __future__ import annotations
 
+import hashlib
 import json
 import math
 import os
@@ -38,10 +40,26 @@ def cache_key(n: int, cams: Sequence, sh_degree: int) -> str:
     return f"{arch}|views{len(cams)}|px2^{round(math.log2(max(px, 1)))}|n2^{round(math.log2(max(n, 1)))}|deg{sh_degree}"
 
 
+def identity(candidates: Sequence[Tuple[int, int, int, int, int]]) -> str:
+    """The library's kernels and the candidates, in a few letters."""
+    h = hashlib.sha256()
+    with open(B.LIB_PATH, "rb") as f:
+        h.update(f.read())
+    h.update(repr([tuple(c) for c in candidates]).encode())
+    return h.hexdigest()[:16]
+
+
+def _cached(entry, ident: str) -> Optional[Tuple[int, int, int, int, int]]:
+    if not isinstance(entry, list) or len(entry) < 3 or entry[2] != ident:
+        return None
+    return tuple(entry[0])
+
+
 def _load() -> Dict[str, list]:
     try:
         with open(_CACHE) as f:
-            return json.load(f)
+            d = json.load(f)
+        return d if isinstance(d, dict) else {}
     except (OSError, ValueError):
         return {}
 
@@ -63,8 +81,10 @@ def tune_batched(make_step, n: int, cams: Sequence, sh_degree: int, replays: int
     {candidate: ms})."""
     key = cache_key(n, cams, sh_degree)
     cache = _load() if use_cache else {}
-    if key in cache:
-        return tuple(cache[key][0]), {}
+    ident = identity(candidates) if use_cache else ""
+    hit = _cached(cache.get(key), ident)
+    if hit:
+        return hit, {}
     times = {}
     for tw, th, dp, bw, sg in candidates:
         opts = B.default_opts(tile_w=tw, tile_h=th, batch_depth=dp, block_w=bw, seg_len=sg)
@@ -90,6 +110,7 @@ def tune_batched(make_step, n: int, cams: Sequence, sh_degree: int, replays: int
     fastest = min(times.values())
     best = next(c for c in times if times[c] <= fastest * (1.0 + TIE))
     if use_cache:
-        cache[key] = [list(best), {f"{a}x{b}/d{c}/b{d}/L{e}": v for (a, b, c, d, e), v in times.items()}]
+        cache[key] = [list(best), {f"{a}x{b}/d{c}/b{d}/L{e}": v for (a, b, c, d, e), v in times.items()},
+                      ident]
         _store(cache)
     return best, times
