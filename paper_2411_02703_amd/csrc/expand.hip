@@ -15,6 +15,8 @@
 //      after ring k every unvisited point is at least k cell sizes away), sixteen lanes a point; a point whose third
 //      neighbour is not settled within kMaxRing rings is searched by brute force, a wave per point.
 // Accepted points are appended after the n_old existing Gaussians in their input order.
+#include <algorithm>
+
 #include "common.h"
 
 namespace {
@@ -169,8 +171,8 @@ __global__ void k_sorted_points(const float* __restrict__ pts, const int32_t* __
                                 const int32_t* __restrict__ count, float4* __restrict__ sp) {
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= count[0]) return;
-  const int i = cv[s];
-  sp[s] = make_float4(pts[3 * i], pts[3 * i + 1], pts[3 * i + 2], __int_as_float(i));
+  const int64_t i = cv[s];
+  sp[s] = make_float4(pts[3 * i], pts[3 * i + 1], pts[3 * i + 2], __int_as_float((int)i));
 }
 
 // The smallest three of `lanes` (a power of two) neighbouring lanes' sorted triples, in every one of them: three rounds
@@ -216,7 +218,7 @@ __global__ __launch_bounds__(256) void k_knn(const float4* __restrict__ sp, cons
                                              const int32_t* __restrict__ off, float* __restrict__ out_ls,
                                              int32_t* __restrict__ brute, int32_t* __restrict__ n_brute) {
   const int64_t A = count[0];
-  const int64_t s = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kKnnLanes;
+  const int64_t s = (((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * blockDim.x + threadIdx.x) / kKnnLanes;
   const int sub = threadIdx.x % kKnnLanes;
   if (s >= A) return;  // (the whole group)
   const float4 p = sp[s];
@@ -389,8 +391,10 @@ hipError_t expand(const gs_params& p, const gs_params& m, const gs_params& v, in
   auto* sp = reinterpret_cast<float4*>((reinterpret_cast<uintptr_t>(scratch + L.sp) + 15) & ~(uintptr_t)15);
   k_sorted_points<<<bm, 256, 0, st>>>(pts, scratch + L.pv1, cnt, sp);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  k_knn<<<(unsigned)((M * kKnnLanes + 255) / 256), 256, 0, st>>>(sp, u64(L.pk1), cnt, cell, scratch + L.off, ls_new,
-                                                                 scratch + L.brute, cnt + 1);
+  // (a dimension of a grid has less than 2^32 threads; 2^28 points take more)
+  const int64_t bk = (M * kKnnLanes + 255) / 256, bx = std::min<int64_t>(bk, 1 << 23);
+  k_knn<<<dim3((unsigned)bx, (unsigned)((bk + bx - 1) / bx)), 256, 0, st>>>(sp, u64(L.pk1), cnt, cell, scratch + L.off,
+                                                                            ls_new, scratch + L.brute, cnt + 1);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   k_knn_brute<<<256, 256, 0, st>>>(sp, cnt, scratch + L.brute, cnt + 1, scratch + L.off, ls_new);
   if ((e = hipGetLastError()) != hipSuccess) return e;
