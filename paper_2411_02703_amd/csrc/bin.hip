@@ -144,12 +144,17 @@ constexpr int kDigitBlocks = 1024;
 
 // Keys per tile of the passes, by the number of keys (known on the device only).  Small sorts want many short blocks,
 // large ones long runs in the output and few states: with 2048 and 8192 keys a tile a pass of 2 k keys takes 5.2 and
-// 9.7 us, of 100 k 64-bit keys 7.3 and 11.9, of 270 k 22.8 and 21.3, of 0.75 M 39 and 30, of 1.5 M 52 and 40.
+// 9.7 us, of 100 k 64-bit keys 7.3 and 11.9, of 270 k 22.8 and 21.3, of 0.75 M 39 and 30, of 1.5 M 52 and 40.  64-bit keys
+// have 4096 a tile as long as that is at most a tile per CU (256): eight passes over 530 k, 1 M and 1.5 M take 126, 155 and
+// 209 us with 4096 and 147, 168 and 181 with 8192 (156, 173 and 200 with a histogram and a scan per digit, which two passes
+// over 1.5 M still do as fast: 49 against 51).  32-bit ones gain nothing: a keyframe step 1576 us with 8192, 1582 with 4096.
 constexpr int kSortThreads = 1024;
-constexpr int kSmallItems = 2, kLargeItems = 8;
-constexpr int64_t kSmallSort = int64_t(1) << 19;
+constexpr int kSmallItems = 2, kMidItems = 4, kLargeItems = 8;
+constexpr int64_t kSmallSort = int64_t(1) << 19, kMidSort = int64_t(1) << 20;
+template <class KeyT>
 __host__ __device__ inline int sort_tile(int64_t n) {
-  return kSortThreads * (n <= kSmallSort ? kSmallItems : kLargeItems);
+  const bool mid = sizeof(KeyT) == 8 && n <= kMidSort;
+  return kSortThreads * (n <= kSmallSort ? kSmallItems : mid ? kMidItems : kLargeItems);
 }
 
 // (The first pass's states are cleared here.)
@@ -161,7 +166,7 @@ __global__ __launch_bounds__(kDigitThreads) void k_sort_digits(const KeyT* __res
                                                                uint32_t* __restrict__ state) {
   __shared__ int h[(int)sizeof(KeyT)][256];
   const int64_t n = sort_count(count_dev, n_sized, cap);
-  const int tile = sort_tile(n);
+  const int tile = sort_tile<KeyT>(n);
   const int64_t words = (n + tile - 1) / tile * 256;
   for (int64_t i = (int64_t)blockIdx.x * kDigitThreads + threadIdx.x; i < words; i += (int64_t)gridDim.x * kDigitThreads)
     state[i] = 0;
@@ -348,11 +353,11 @@ __global__ __launch_bounds__(kSortThreads, sizeof(KeyT) == 4 ? 8 : 4) void k_sor
     uint32_t* state, uint32_t* next) {
   __shared__ SortStage<KeyT> s;
   const int64_t n = sort_count(count_dev, n_sized, cap);
-  if ((int64_t)blockIdx.x * sort_tile(n) >= n) return;  // (as many blocks as tiles go on)
+  if ((int64_t)blockIdx.x * sort_tile<KeyT>(n) >= n) return;  // (as many blocks as tiles go on)
   const int tid = threadIdx.x;
   if (tid == 0) {  // (the minimum: where another sort meddles with the tickets, the tile is one of this sort's all the same)
     const uint32_t ticket = (uint32_t)atomicAdd(digits + kCopies * 256 * passes + pass, 1);
-    s.tile = (int)min(ticket, (uint32_t)((n - 1) / sort_tile(n)));
+    s.tile = (int)min(ticket, (uint32_t)((n - 1) / sort_tile<KeyT>(n)));
   }
   for (int i = tid; i < kSortThreads / 64 * 256; i += kSortThreads) (&s.cnt[0][0])[i] = 0;
   int dc = 0;  // the digit's keys
@@ -363,6 +368,8 @@ __global__ __launch_bounds__(kSortThreads, sizeof(KeyT) == 4 ? 8 : 4) void k_sor
   __syncthreads();
   if (n <= kSmallSort)
     scatter_tile<KeyT, kSmallItems>(s, kin, vin, kout, vout, n, pass, dc, state, next);
+  else if (sizeof(KeyT) == 8 && n <= kMidSort)
+    scatter_tile<KeyT, kMidItems>(s, kin, vin, kout, vout, n, pass, dc, state, next);
   else
     scatter_tile<KeyT, kLargeItems>(s, kin, vin, kout, vout, n, pass, dc, state, next);
 }
@@ -1022,11 +1029,12 @@ hipError_t fill_f32(float* p, float v, int64_t n, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tiles of a sort of up to n keys, and its two passes' states.
+// Tiles of a sort of up to n keys, and its two passes' states.  (The 4096-key tiles of 64-bit keys are at most as many as
+// the 2048-key ones of kSmallSort.)
 static int64_t sort_blocks(int64_t n) {
   if (n < 1) n = 1;
   const int64_t few = n < kSmallSort ? n : kSmallSort;
-  const int64_t small = cdiv(few, sort_tile(few)), large = cdiv(n, sort_tile(n));
+  const int64_t small = cdiv(few, kSortThreads * kSmallItems), large = cdiv(n, kSortThreads * kLargeItems);
   return small > large ? small : large;
 }
 static size_t state_ints(int64_t n) { return 512 * (size_t)sort_blocks(n); }
