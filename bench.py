@@ -27,8 +27,10 @@ OPS_EVAL = 14 + 4
 OPS_CONTRIB_FWD = 10
 OPS_CONTRIB_BWD = 55 + 4
 # The same work counted from this build's own per-pair code (multiply-add as one, exp and reciprocal as
-# four); evaluated pairs are evaluated in both sweeps of the fused kernel.
-OWN_EVAL, OWN_CONTRIB_FWD, OWN_CONTRIB_BWD = 19, 9, 37
+# four); evaluated pairs are evaluated in both sweeps of the fused kernel.  Of the backward's 27 operations a
+# contributing pair the eight multiply-adds with the colour and depth gradients run on the matrix cores; what the
+# scans over a row of lanes and the lanes without a pair add is not counted.
+OWN_EVAL, OWN_CONTRIB_FWD, OWN_CONTRIB_BWD = 16, 9, 27
 # MI355X: 256 CUs x 4 SIMD x 16 lanes at 2.4 GHz, one VALU lane-operation per lane per cycle.
 ALU_PEAK = 256 * 4 * 16 * 2.4e9
 HBM_PEAK = 8.0e12  # bytes/s

@@ -154,12 +154,12 @@ typedef struct gs_frame {
                            backward first sums each record of big_rec into its first slot and sets that slot's
                            last word to 1 */
   int32_t* inst_first;  /* [n]: exclusive scan of n_inst; for g a multiple of 64, the first partial slot of the
-                           64 Gaussians from g */
+                           64 Gaussians from g (for callers: no kernel reads it) */
   uint64_t* vis_mask;   /* [n]: bit v set if Gaussian g is visible in view v */
   int32_t* n_inst;      /* [n]: tile instances of Gaussian g over all views */
   int32_t* n_rec;       /* [n]: visible records (views) of Gaussian g */
   int32_t* rec_first;   /* [n]: exclusive scan of n_rec; the records of the 64 Gaussians from g (g a multiple of
-                           64) start at rec_first[g] in the record list */
+                           64) start at rec_first[g] in the record list (for callers: no kernel reads it) */
   uint32_t* zbits;      /* [n_views*n]: IEEE bits of the camera depth of each visible record */
   int32_t* rec_slot;    /* [n_views*n]: first partial slot of each visible record */
   int32_t* big_rec;     /* [rec_cap]: the records with more than 32 tile instances (count in counters[198]); the

@@ -13,9 +13,12 @@ constexpr int kWave = 64;
 constexpr int kLossSlots = 32;
 
 // Frames of at least this many tiles run the forward of the backward's whole tiles in the kernel of the segments'
-// sums (where it issues 1.7 times as fast) and keep its result in a state slot per work item; smaller frames, which
-// leave the chip partly idle and wait for their longest tile, run it in the backward's kernel (48 tiles of 54 records:
-// 20 us in one kernel, 11 + 21 us in two).
+// sums (at six waves a SIMD instead of four) and keep its result in a state slot per work item; smaller frames, which
+// leave the chip partly idle and wait for their longest tile, run it in the backward's kernel.  A training step with the
+// forward in the sums' kernel and in the backward's: 252 tiles of 16x16 with 13 records 100 and 94 us, 1008 with 32 146
+// and 141, 2028 with 56 212 and 207; a keyframe of 6.7 k tiles 1585 and 1604, odd views of 32x8 tiles 466 and 480, one
+// active view of 24 1357 and 1366; 24 views of 16x8 tiles 6240 and 6225.  Frames of random Gaussians lie within 2% either
+// way up to 200 k tiles (16x16 above 200 records a tile gain, 16x8 and 8x8 lose).
 constexpr int kWholeTiles = 2048;
 
 // Slots of a frame's segment state (none where lists are never split, seg_cap = 0: k_render_bwd keeps no state).
@@ -79,22 +82,6 @@ __device__ __forceinline__ float wave_sum_last(float x) {
   return x;
 }
 
-// Maximum over the 64 lanes of a non-negative int, returned to every lane (same DPP pattern as above).
-template <int CTRL, int ROW_MASK = 0xf>
-__device__ __forceinline__ int dpp_i(int x) {
-  return __builtin_amdgcn_update_dpp(0, x, CTRL, ROW_MASK, 0xf, true);
-}
-
-__device__ __forceinline__ int wave_max_nonneg(int x) {
-  x = max(x, dpp_i<0xB1>(x));
-  x = max(x, dpp_i<0x4E>(x));
-  x = max(x, dpp_i<0x141>(x));
-  x = max(x, dpp_i<0x140>(x));
-  x = max(x, dpp_i<0x142, 0xa>(x));
-  x = max(x, dpp_i<0x143, 0xc>(x));
-  return __builtin_amdgcn_readlane(x, 63);
-}
-
 // A value known to be the same in every lane, moved to scalar registers.
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
@@ -102,14 +89,14 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-// Exclusive prefix sum over the 64 lanes (lane order) of a non-negative int; total = the wave's sum.
 // The value of the lane n before in its row of 16 (0 from outside the row), or of lane 15 of the row before (rows 1 and
 // 3), or of lane 31 (rows 2 and 3): the steps of a scan over the wave.  (In registers; a __shfl_up costs an LDS trip.)
 template <int CTRL, int ROWS = 0xf>
 __device__ __forceinline__ int dpp_or_zero(int x) {
   return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xf, ROWS == 0xf);
 }
-// Called with every lane of the wave active.
+// Exclusive prefix sum over the 64 lanes (lane order) of a non-negative int; total = the wave's sum.  Called with every
+// lane of the wave active.
 __device__ __forceinline__ int wave_excl_scan(int x, int& total) {
   int incl = x;
   incl += dpp_or_zero<0x111>(incl);
@@ -184,13 +171,6 @@ constexpr int kWideRecord = 32;
 
 // Hardware float atomic add without return (global_atomic_add_f32).
 __device__ __forceinline__ void atomic_add_f32(float* p, float v) { unsafeAtomicAdd(p, v); }
-
-// Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous range of work items
-// so neighbouring tiles (which share Gaussians) meet in the same L2.
-__device__ __forceinline__ int xcd_remap(int b, int nblocks) {
-  const int per = (nblocks + 7) >> 3;
-  return (b & 7) * per + (b >> 3);
-}
 
 // View of a global tile: largest v with tile_offset <= tile (n_views <= 64; every lane of the wave asks for the same
 // tile).  Past a few views the lanes read an offset each: a scalar loop waits for one load after the other.
@@ -310,7 +290,6 @@ size_t order_scratch_ints(int64_t n);
 hipError_t spatial_order(const gs_params& p, const gs_params& m, const gs_params& v, const gs_params& op,
                          const gs_params& om, const gs_params& ov, int32_t* perm_out, int32_t* scratch,
                          hipStream_t s);
-// The step counter and bias corrections of one Adam step (skipped when *skip_flags has the overflow bit).
 // Projection backward fused with Adam: params, m, v updated in place; the gradient is written to grads_out
 // when it is non-NULL.  The step's count and bias corrections are advanced in passing.
 hipError_t project_bwd_adam(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params& m,

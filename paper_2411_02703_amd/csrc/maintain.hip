@@ -48,8 +48,8 @@ Rows rows_of(const gs_params& p, const gs_params& m, const gs_params& v, const g
 constexpr int kRowBlock = 256;
 
 // Rows a block copies: some 4 k words of an array set, and few where there are few Gaussians.  Prune of 1M at 64, 128 and
-// 256 rows: degree 0 163, 129, 92 us; degree 2 217, 202, 208; degree 3 282, 297, 310; of 2000 of degree 3 18.3, 19.2,
-// 20.6 (the reorder's random reads hardly differ).
+// 256 rows: degree 0 163, 129, 92 us; degree 2 217, 202, 208; degree 3 282, 297, 310.  Of 6 k of degree 0 22.7, 22.9, 23.1,
+// of 12 k 23.0, 23.2, 23.5, of 24 k 24.3, 23.8, 24.0, of 40 k 26.1, 25.0, 24.8 (the reorder's random reads hardly differ).
 inline int rows_per_block(int64_t n, int sh_degree) {
   return n < (int64_t(1) << 14) || sh_degree >= 3 ? 64 : sh_degree == 2 ? 128 : 256;
 }

@@ -731,7 +731,11 @@ template <bool ADAM>
 static hipError_t project_bwd_launch(const gs_params& p, const gs_frame& f, const gs_opts& o, const gs_params* gr,
                                      const AdamArgs& ad, const gsk::LossSum& ls, const gsk::AdamPrep& ap,
                                      hipStream_t st) {
-  // few Gaussians: a wave a block, so that they spread over the CUs (2915 Gaussians of degree 3 in 14 views: 85 -> 77 us)
+  // Few Gaussians: a wave a block, so that they spread over the CUs.  A block of either size reserves LDS for four waves,
+  // so that at most three waves of the short ones share a CU: at degree 3 the line lies where 256 CUs are full.  The
+  // projection backward of 14 views with blocks of 64 and 256: 4 k Gaussians of degree 3 35 and 40 us, 32 k 46 and 51, 40 k
+  // 48 and 52, 65 k 89 and 53; of degree 0 4 k 23 and 25, 32 k 30 and 31, 65 k 34 and 34; of one view 10 and 9 throughout
+  // (a step of one view takes as long with both).
   const int threads = p.n <= 32768 ? 64 : 256;
   const int blocks = (int)((p.n + threads - 1) / threads);
   const DevOpts op = gsk::dev_opts(o);

@@ -45,7 +45,7 @@ struct Geo {
 
 // The backward's geometry: rounds of 128 records whatever the forward uses.  Each wave sums its records' gradients
 // in its own LDS rows (40 bytes a record), which set the round's size: 128 leaves four waves a SIMD at every tile
-// shape.
+// shape (three at 16x16 and 32x8 where the forward stages two records a thread, whose round shares the block's LDS).
 template <int TW, int TH>
 using BGeo = Geo<TW, TH, 1, (TW * TH >= 128 ? 128 : 64)>;
 
@@ -541,7 +541,7 @@ __device__ __forceinline__ void pixel_upstream(const TileCtx& t, const BwdArgs& 
 }
 
 // Stores the workgroup's loss as that of the tile at schedule position `at` (every thread must call it).  Plain stores,
-// added up by k_loss_total: atomics into one or two cache lines take about 5 ns each whichever words they hit, which
+// added up by sum_losses: atomics into one or two cache lines take about 5 ns each whichever words they hit, which
 // had made frames of many short tiles wait for them (22 k tiles: 123 us).
 template <class G>
 __device__ __forceinline__ void store_loss(const TileCtx& t, const BwdArgs& a, int at, float loss_acc) {
@@ -1039,15 +1039,16 @@ __device__ __forceinline__ void for_items(int count, int32_t* ctr, Body body) {
 
 // A whole tile of 1 to kOwnForward - 1 records has its forward in the backward's block instead of k_bwd_sums: the sums
 // that k_bwd_sums leaves behind (20 B written and read per pixel) cost as much as a very short list's sweep, which the
-// backward's kernel runs at half the waves.  Both kernels together with the line at 2, 8 and 32: 28 k tiles of 32x8 with
-// some 12 records each 406, 409 and 422 us; 16.5 k tiles of 16x8 with 13 143, 146 and 147; 24 views 3022, 3007 and 2993.
+// backward's kernel runs at two thirds of the waves.  Steps with the line at 2, 8 and 32: 14.8 k tiles of 32x8 with some
+// 23 records each 521, 525 and 538 us; 29.7 k of 16x8 with 21 522, 525 and 539; 24 views 6.31, 6.32 and 6.33 ms.
 constexpr int kOwnForward = 8;
 
 // Step 1 of the backward: segments of the split tiles run segment_sums; whole tiles run the forward sweep up to the
 // upstream gradient and leave it (g and S, six floats a pixel) in the segment state's slot of their work item (with
 // forward images, and in small frames, k_bwd_main forms it itself).  A kernel of its own, since the forward's walk
-// needs half the registers and a third of the LDS of the backward's: at eight waves a SIMD it issues 1.7 times as
-// fast as inside the backward's kernel.
+// needs 80 of the backward's 128 registers and half of its LDS (21.6 of 34 KB at 16x16 and 32x8, 8.7 of 19.6 at 16x8, 3.8
+// of 7.2 at 8x8): six waves a SIMD instead of four (kWholeTiles has what that is worth).  With two records a thread (50.8
+// KB, the staged records in scratch) three, which is why that never wins.
 template <int TW, int TH, int DEPTH, bool HAVE_FWD, bool LOSS, bool PERSIST = false>
 __global__ __launch_bounds__(TW * TH, 6) void k_bwd_sums(const float4* __restrict__ rec, const int32_t* __restrict__ vals,
                                                       const int2* __restrict__ range,
